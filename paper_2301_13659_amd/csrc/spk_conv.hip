@@ -140,6 +140,9 @@ static spk_status conv_run(const char *what, const uint8_t *in_times, int B, int
     SPK_REQUIRE((long long)B * Ho * Wo < (1LL << 31) && (long long)Ci * Hi * Wi < (1LL << 31),
                 SPK_E_SHAPE, "%s: layer too large", what);
     hipStream_t s = spk::stream_of(stream);
+    // (a pooled call's unpooled map is not the layer's input: it takes the paths below)
+    if (!pool && spk::fc_fire_supported(T, Hi, Wi, Kh, Kw, pad, readout, potentials != nullptr))
+        return spk::fc_fire(in_times, B, T, Ci, w, half_w, Co, theta, readout, out_times, out_vkey, s);
     if (spk::conv_pt_supported(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, half_w, readout,
                                potentials != nullptr))
         return spk::conv_fire_pt(in_times, B, T, Ci, Hi, Wi, w, half_w, Co, Kh, Kw, stride, pad, Ho, Wo,

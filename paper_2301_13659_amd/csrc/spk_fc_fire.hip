@@ -1,0 +1,302 @@
+// spk_fc_fire, and convolutions of a 1 x 1 kernel on a 1 x 1 image, which are
+// the same layer (Spyker §II-E.2, §II-E.1 Eq. 2): V_t[b, o] = sum_i W[o, i] *
+// [in_times[b, i] <= t], first-spike firing of §II-D.3.
+//
+// One launch with no packing pass: both operands are already laid out along
+// the depth i, so a lane's eight taps of a fragment are eight consecutive
+// bytes of in_times (a sample's row) and eight consecutive weights (a map's
+// row), loaded straight into registers.  Rows of a 32x32x16 tile are (sample,
+// step) pairs, TP steps per sample (readout: one, step T - 1); float masters
+// become hi/lo halves in registers (two products per slice).
+//
+// What bounds it: at these sizes (tens of megaflops) the latency of a wave's
+// chain of slices, so the depth is split over the eight waves of a block,
+// which add their partial tiles through LDS in wave order (repeated runs agree
+// bit for bit); a block owns kR row tiles x kC column tiles so that each
+// weight fragment, whose hi/lo split costs 24 vector instructions, serves kR
+// products.  256 samples x 1125 inputs x 211 maps at T = 15 with float
+// masters: 66.2 ms before (a thread per output neuron of the direct kernel:
+// the layer's rows exceed the staging of the convolution kernels), 14 us now.
+#include <hip/hip_fp16.h>
+
+#include "spk_internal.h"
+
+namespace {
+
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+
+constexpr int kWaves = 8;           // depth splits of a block
+constexpr int kC = 2;               // column tiles (32 maps) per block
+constexpr uint32_t kSelLo = 0x04010400u;  // bytes 0,1 -> halves 1024 + b
+constexpr uint32_t kSelHi = 0x04030402u;  // bytes 2,3 -> halves 1024 + b
+
+struct FcGeom {
+    int B, T, I, O;
+    int S;       // 16-tap slices of the depth
+    int NT;      // column tiles
+    int t_last;  // readout: T - 1
+};
+
+__device__ __forceinline__ uint32_t upto2(uint32_t x, h2 c)
+{
+    const h2 one = {(_Float16)1.0f, (_Float16)1.0f}, zero = {(_Float16)0.0f, (_Float16)0.0f};
+    const h2 a = c - __builtin_bit_cast(h2, x);  // halves 1024 + t: >= 1 iff t <= the row's step
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_elementwise_max(a, zero), one));
+}
+
+__device__ __forceinline__ h8 frag_upto(uint2 x, h2 c)
+{
+    const u4 v = {upto2(__builtin_amdgcn_perm(0x64646464u, x.x, kSelLo), c),
+                  upto2(__builtin_amdgcn_perm(0x64646464u, x.x, kSelHi), c),
+                  upto2(__builtin_amdgcn_perm(0x64646464u, x.y, kSelLo), c),
+                  upto2(__builtin_amdgcn_perm(0x64646464u, x.y, kSelHi), c)};
+    return __builtin_bit_cast(h8, v);
+}
+
+// TP: steps per sample in a tile (8, 16, 32; 1: readout).  Row r of a tile:
+// the sample slot and the step, such that a lane's sixteen output elements
+// (element e of wave half hh is row 8*(e/4) + 4*hh + e%4) are whole runs of
+// steps in order for TP = 8 and 16, as in spk_conv_pt.hip.
+template <int TP>
+__device__ __forceinline__ void row_slot_step(int r, int &slot, int &step)
+{
+    const int hi = r >> 3, half = (r >> 2) & 1, lo = r & 3;
+    if (TP == 1) {
+        slot = r;
+        step = 0;
+    } else if (TP == 8) {
+        slot = 2 * (hi >> 1) + half;
+        step = ((hi & 1) << 2) | lo;
+    } else if (TP == 16) {
+        slot = half;
+        step = (hi << 2) | lo;
+    } else {
+        slot = 0;
+        step = r;
+    }
+}
+
+struct Frag {  // one slice of a wave's operands, as loaded
+    uint2 x[4];
+    float w[kC][8];
+    uint4 h[kC];
+};
+
+template <int NP, int TP, int kR>
+__global__ __launch_bounds__(64 * kWaves) void k_fc_fire(const uint8_t *__restrict__ in,
+                                                         const void *__restrict__ wv, FcGeom g,
+                                                         float theta, uint8_t *__restrict__ out_t,
+                                                         float *__restrict__ out_v)
+{
+    constexpr int kSlots = 32 / TP;  // samples per row tile
+    extern __shared__ float part[];  // [wave][tile][element][lane]
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane & 31, hh = lane >> 5;
+    const int ct0 = blockIdx.y * kC;
+    const int b0 = blockIdx.x * kR * kSlots;
+    int slot, step;
+    row_slot_step<TP>(r, slot, step);
+    const uint32_t cb = 0x6401u + (uint32_t)(TP == 1 ? g.t_last : min(step, g.T - 1));
+    const h2 cc = __builtin_bit_cast(h2, cb | (cb << 16));
+    // rows past the last sample and maps past the last repeat the last (not stored)
+    const uint8_t *xr[kR];
+#pragma unroll
+    for (int i = 0; i < kR; i++) xr[i] = in + (size_t)min(b0 + i * kSlots + slot, g.B - 1) * g.I + 8 * hh;
+    const char *wr[kC];
+#pragma unroll
+    for (int c = 0; c < kC; c++)
+        wr[c] = reinterpret_cast<const char *>(wv) +
+                ((size_t)min((ct0 + c) * 32 + r, g.O - 1) * g.I + 8 * hh) * (NP == 2 ? 4 : 2);
+
+    f16v acc[kR][kC];
+#pragma unroll
+    for (int i = 0; i < kR; i++)
+#pragma unroll
+        for (int c = 0; c < kC; c++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) acc[i][c][e] = 0.0f;
+
+    // this wave's slices
+    const int s0 = wave * g.S / kWaves, s1 = (wave + 1) * g.S / kWaves;
+    auto load = [&](int s) {
+        Frag f;
+        if (16 * s + 16 <= g.I) {
+#pragma unroll
+            for (int i = 0; i < kR; i++) __builtin_memcpy(&f.x[i], xr[i] + 16 * s, 8);
+#pragma unroll
+            for (int c = 0; c < kC; c++) {
+                if (NP == 2) __builtin_memcpy(f.w[c], wr[c] + 64 * s, 32);
+                else __builtin_memcpy(&f.h[c], wr[c] + 32 * s, 16);
+            }
+        } else {  // the depth's ragged end: taps past I never fire, their weights are zero
+            const int left = g.I - 16 * s - 8 * hh;
+#pragma unroll
+            for (int i = 0; i < kR; i++) {
+                uint32_t q[2] = {0xFFFFFFFFu, 0xFFFFFFFFu};
+#pragma unroll
+                for (int e = 0; e < 8; e++)
+                    if (e < left)
+                        q[e >> 2] = (q[e >> 2] & ~(0xFFu << (8 * (e & 3)))) |
+                                    ((uint32_t)xr[i][16 * s + e] << (8 * (e & 3)));
+                f.x[i] = make_uint2(q[0], q[1]);
+            }
+#pragma unroll
+            for (int c = 0; c < kC; c++) {
+                if (NP == 2) {
+#pragma unroll
+                    for (int e = 0; e < 8; e++)
+                        f.w[c][e] = e < left ? reinterpret_cast<const float *>(wr[c] + 64 * s)[e] : 0.0f;
+                } else {
+                    uint32_t q[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+                    for (int e = 0; e < 8; e++)
+                        if (e < left)
+                            q[e >> 1] |= (uint32_t)reinterpret_cast<const uint16_t *>(wr[c] + 32 * s)[e] << (16 * (e & 1));
+                    f.h[c] = make_uint4(q[0], q[1], q[2], q[3]);
+                }
+            }
+        }
+        return f;
+    };
+    auto use = [&](const Frag &f) {
+        h8 bw[kC][NP];
+#pragma unroll
+        for (int c = 0; c < kC; c++) {
+            if (NP == 2) {
+#pragma unroll
+                for (int e = 0; e < 8; e++) {
+                    const _Float16 hi = (_Float16)f.w[c][e];
+                    bw[c][0][e] = hi;
+                    bw[c][NP - 1][e] = (_Float16)(f.w[c][e] - (float)hi);
+                }
+            } else {
+                bw[c][0] = __builtin_bit_cast(h8, f.h[c]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kR; i++) {
+            const h8 a = frag_upto(f.x[i], cc);
+#pragma unroll
+            for (int c = 0; c < kC; c++)
+#pragma unroll
+                for (int k = 0; k < NP; k++)
+                    acc[i][c] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, bw[c][k], acc[i][c], 0, 0, 0);
+        }
+    };
+    if (s0 < s1) {
+        Frag cur = load(s0);
+        for (int s = s0; s < s1; s++) {
+            Frag nxt = cur;
+            if (s + 1 < s1) nxt = load(s + 1);
+            use(cur);
+            cur = nxt;
+        }
+    }
+
+    // partial tiles to LDS; tile i of the block is then summed over the waves
+    // in order by wave i % kWaves
+#pragma unroll
+    for (int i = 0; i < kR * kC; i++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) part[((wave * kR * kC + i) * 16 + e) * 64 + lane] = acc[i / kC][i % kC][e];
+    __syncthreads();
+    for (int i = wave; i < kR * kC; i += kWaves) {
+        f16v v;
+#pragma unroll
+        for (int e = 0; e < 16; e++) v[e] = 0.0f;
+#pragma unroll
+        for (int q = 0; q < kWaves; q++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) v[e] += part[((q * kR * kC + i) * 16 + e) * 64 + lane];
+        const int o = (ct0 + i % kC) * 32 + r;
+        const int bt = b0 + (i / kC) * kSlots;
+        auto store = [&](int b, uint32_t t, float key) {
+            if (b < g.B && o < g.O) {
+                out_t[(size_t)b * g.O + o] = (uint8_t)t;
+                out_v[(size_t)b * g.O + o] = key;
+            }
+        };
+        if constexpr (TP == 1) {
+#pragma unroll
+            for (int e = 0; e < 16; e++) store(bt + 8 * (e >> 2) + 4 * hh + (e & 3), spk::kNever, v[e]);
+        } else if constexpr (TP == 32) {
+            // the lane's steps in order, then the earlier of the two wave halves
+            uint32_t t = spk::kNever;
+            float key = 0.0f;
+#pragma unroll
+            for (int e = 15; e >= 0; e--) {
+                const bool c = v[e] > theta;
+                t = c ? (uint32_t)(8 * (e >> 2) + 4 * hh + (e & 3)) : t;
+                key = c ? v[e] : key;
+            }
+            const uint32_t t2 = (uint32_t)__shfl_xor((int)t, 32);
+            const float key2 = __shfl_xor(key, 32), last = __shfl(v[15], 32 + r);
+            if (t2 < t) {
+                t = t2;
+                key = key2;
+            }
+            if (t == (uint32_t)spk::kNever) key = last;
+            if (hh == 0) store(bt, t, key);  // (rows past T - 1 repeat it, so t < T)
+        } else {
+#pragma unroll
+            for (int k = 0; k < 16 / TP; k++) {
+                uint32_t t = spk::kNever;
+                float key = v[k * TP + TP - 1];
+#pragma unroll
+                for (int e = TP - 1; e >= 0; e--) {
+                    const bool c = v[k * TP + e] > theta;
+                    t = c ? (uint32_t)e : t;
+                    key = c ? v[k * TP + e] : key;
+                }
+                store(bt + (TP == 8 ? 2 * k + hh : hh), t, key);
+            }
+        }
+    }
+}
+
+template <int NP, int TP, int kR>
+void launch(dim3 grid, hipStream_t s, const uint8_t *in, const void *w, const FcGeom &g, float theta,
+            uint8_t *out_t, float *out_v)
+{
+    constexpr size_t lds = (size_t)kWaves * kR * kC * 16 * 64 * sizeof(float);
+    static_assert(lds <= 160 * 1024, "partial tiles fit a CU's LDS");
+    auto kern = k_fc_fire<NP, TP, kR>;
+    static const bool attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 (int)lds) == hipSuccess;
+    (void)attr;
+    hipLaunchKernelGGL(kern, grid, dim3(64 * kWaves), lds, s, in, w, g, theta, out_t, out_v);
+}
+
+typedef void (*Launch)(dim3, hipStream_t, const uint8_t *, const void *, const FcGeom &, float, uint8_t *, float *);
+#define SPK_FC(TP) {{&launch<1, TP, 1>, &launch<1, TP, 2>}, {&launch<2, TP, 1>, &launch<2, TP, 2>}}
+const Launch kLaunch[4][2][2] = {SPK_FC(1), SPK_FC(8), SPK_FC(16), SPK_FC(32)};
+#undef SPK_FC
+
+}  // namespace
+
+namespace spk {
+
+bool fc_fire_supported(int T, int Hi, int Wi, int Kh, int Kw, int pad, bool readout, bool potentials)
+{
+    return !potentials && Hi == 1 && Wi == 1 && Kh == 1 && Kw == 1 && pad == 0 && (readout || T <= 32);
+}
+
+spk_status fc_fire(const uint8_t *in, int B, int T, int I, const void *w, bool half_w, int O, float theta,
+                   bool readout, uint8_t *out_t, float *out_v, hipStream_t s)
+{
+    const FcGeom g{B, T, I, O, (I + 15) / 16, (O + 31) / 32, T - 1};
+    const int tp = readout ? 0 : (T <= 8 ? 1 : (T <= 16 ? 2 : 3));
+    const int slots = readout ? 32 : (T <= 8 ? 4 : (T <= 16 ? 2 : 1));
+    const int rows = ceil_div(B, slots), cols = ceil_div(g.NT, kC);
+    // two row tiles per block once one each already gives every CU a block
+    const int two = (long long)rows * cols > 256 ? 1 : 0;
+    kLaunch[tp][half_w ? 0 : 1][two](dim3(ceil_div(rows, two + 1), cols), s, in, w, g, theta, out_t, out_v);
+    return check_launch("spk_conv_fire");
+}
+
+}  // namespace spk

@@ -141,6 +141,11 @@ spk_status conv_fire_pt(const uint8_t *in, int B, int T, int Ci, int Hi, int Wi,
                         bool half_w, int Co, int Kh, int Kw, int stride, int pad, int Ho, int Wo,
                         float theta, uint8_t *out_t, float *out_v, void *ws, hipStream_t s,
                         const PoolIn *pool = nullptr);
+// Fully connected layers (1 x 1 kernels on a 1 x 1 image): readouts, and
+// firing layers with T <= 32, in one launch without scratch (spk_fc_fire.hip).
+bool fc_fire_supported(int T, int Hi, int Wi, int Kh, int Kw, int pad, bool readout, bool potentials);
+spk_status fc_fire(const uint8_t *in, int B, int T, int I, const void *w, bool half_w, int O, float theta,
+                   bool readout, uint8_t *out_t, float *out_v, hipStream_t s);
 // Readout layers (theta = +inf, no dense potentials): the split-K GEMM of the
 // last frame on the same channels-last copy (spk_conv_fast.hip).  packed_w:
 // nullable B fragments from spk_conv_pack_weights, used instead of packing w;
