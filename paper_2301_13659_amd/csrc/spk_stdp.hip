@@ -1,7 +1,8 @@
 // spk_stdp_update: STDP and R-STDP on the winners' receptive fields
 // (Spyker §II-F.1 Eq. 4-6, §II-F.2 Eq. 7).
 //
-// Scatter-free: one workgroup owns kernel o.  It gathers, in (sample, slot)
+// Scatter-free: one workgroup owns kernel o (several split the synapses of
+// kernels over kSplitTaps, see k_stdp_wide).  It gathers, in (sample, slot)
 // order, the winners of map o (an ordered ballot compaction into LDS), and
 // every thread accumulates the changes of its synapses over that list in a
 // fixed order, so the float sums are reproducible.  The clamp and the
@@ -135,7 +136,7 @@ __global__ __launch_bounds__(kThreads) void k_stdp(float *__restrict__ w, uint16
             // G groups of `taps` threads share the winners (group g takes
             // winners g, g + G, ...); the G partial sums are added to D in
             // group order, so the result is the same on every run.
-            const int G = taps <= kThreads / 2 ? min(n_chunk, kThreads / taps) : 1;
+            const int G = min(n_chunk, kThreads / taps);  // (taps <= kSplitTaps here)
             if (G > 1) {
                 if (threadIdx.x < G * taps) {
                     const int grp = threadIdx.x / taps, j = threadIdx.x - grp * taps;
@@ -167,6 +168,166 @@ __global__ __launch_bounds__(kThreads) void k_stdp(float *__restrict__ w, uint16
             __half h = __float2half_rn(v);
             w16[at] = *reinterpret_cast<uint16_t *>(&h);
         }
+    }
+}
+
+// Kernels of more than kSplitTaps synapses: the synapses of map o are split
+// over blocks of kWide, each of which lists map o's winners itself and adds
+// them one by one in list order, so the sums are those of one block per map
+// bit for bit.  Bound by the latency of the scattered one-byte pre-spike loads
+// (16 of a synapse's in flight) along the longest list.  One block per map
+// walked 6,250 synapses x up to 200 winners alone in the batch-256 readout:
+// 182 us against 24 us here; 576 synapses x 16 winners of the spike-input
+// layer took 27 us, 20 us here; 1,125 synapses of a fully connected layer 12
+// us, 10 us here.  (k_stdp keeps the smaller kernels: its threads share the
+// winners of a map, which the documented order of the sums prescribes.)
+constexpr int kSplitTaps = 512;
+constexpr int kWide = 256;             // synapses and threads per block
+constexpr int kScan = 4;               // candidates per thread and round
+constexpr int kRound = kWide * kScan;  // winner slots listed per round
+
+__global__ __launch_bounds__(kWide) void k_stdp_wide(float *__restrict__ w, uint16_t *__restrict__ w16,
+                                                     const uint8_t *__restrict__ in_times,
+                                                     const spk_winner *__restrict__ winners,
+                                                     const int32_t *__restrict__ n_winners,
+                                                     const int32_t *__restrict__ winner_cfg,
+                                                     StdpGeom g, StdpCfgs cfg)
+{
+#pragma clang fp contract(off)
+    __shared__ int4 list_at[kRound];  // window origin: flat input offset (lo, hi), y, x
+    __shared__ int4 list_ra[kRound];  // t_post, a_causal, a_anticausal, stabilize
+    __shared__ int cnt[kScan * (kWide / 64)];
+    __shared__ float s_rate[kMaxCfg][2];
+    __shared__ int s_stab[kMaxCfg];
+    const int o = blockIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int taps = g.Ci * g.Kh * g.Kw, KK = g.Kh * g.Kw;
+    const float L = cfg.c[0].lower, U = cfg.c[0].upper;
+    if ((int)threadIdx.x < cfg.n) {  // (read after the first barrier below)
+        s_rate[threadIdx.x][0] = cfg.c[threadIdx.x].a_causal;
+        s_rate[threadIdx.x][1] = cfg.c[threadIdx.x].a_anticausal;
+        s_stab[threadIdx.x] = cfg.c[threadIdx.x].stabilize;
+    }
+    const int j = blockIdx.y * kWide + threadIdx.x;
+    const bool live = j < taps;
+    const int jc = live ? j : 0;
+    const int c = jc / KK, r = jc - c * KK;
+    const int ky = r / g.Kw, kx = r - ky * g.Kw;
+    const size_t at_w = (size_t)o * taps + jc;
+    const float w0 = w[at_w];
+    const float wl = w0 - L, wu = U - w0;
+    const int rel = (c * g.Hi + ky) * g.Wi + kx;  // this synapse's input from a window origin
+    const int total = g.B * g.k;
+    const uint32_t inv_k = g.k > 1 ? (uint32_t)(0x100000000ull / (uint32_t)g.k) : 0u;
+    float acc = 0.0f;
+    int n_total = 0;
+    for (int base = 0; base < total; base += kRound) {
+        // ordered list of this round's winners of map o: candidate u of a
+        // thread is slot base + u * kWide + threadIdx.x.  Most slots hold
+        // another map: only its own are looked at further.
+        int cand[kScan];
+        bool keep[kScan];
+        int bs[kScan], qs[kScan];
+        uint64_t m[kScan];
+#pragma unroll
+        for (int u = 0; u < kScan; u++)
+            cand[u] = winners[min(base + u * kWide + (int)threadIdx.x, total - 1)].c;
+#pragma unroll
+        for (int u = 0; u < kScan; u++) {
+            const int i = base + u * kWide + (int)threadIdx.x;
+            keep[u] = i < total && cand[u] == o;
+            bs[u] = i;
+            qs[u] = 0;
+            if (keep[u]) {
+                int slot = 0;
+                if (g.k > 1) {  // i / k: the product is the quotient or one less
+                    bs[u] = (int)__umulhi((uint32_t)i, inv_k);
+                    slot = i - bs[u] * g.k;
+                    if (slot >= g.k) {
+                        bs[u]++;
+                        slot -= g.k;
+                    }
+                }
+                if (winner_cfg) qs[u] = winner_cfg[i];
+                keep[u] = slot < n_winners[bs[u]] && qs[u] >= 0 && qs[u] < cfg.n;
+            }
+            m[u] = __ballot(keep[u]);
+            if (lane == 0) cnt[u * (kWide / 64) + wave] = __popcll(m[u]);
+        }
+        __syncthreads();
+        // slots in front of each (u, wave): a scan over the counts
+        constexpr int kCounts = kScan * (kWide / 64);
+        static_assert(kCounts <= 64, "one count per lane");
+        int scan = lane < kCounts ? cnt[lane] : 0;
+#pragma unroll
+        for (int d = 1; d < kCounts; d <<= 1) {
+            const int v = __shfl_up(scan, d);
+            if (lane >= d) scan += v;
+        }
+        const int n = __builtin_amdgcn_readlane(scan, kCounts - 1);
+#pragma unroll
+        for (int u = 0; u < kScan; u++) {
+            const int end = __shfl(scan, u * (kWide / 64) + wave);
+            if (keep[u]) {
+                const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m[u] >> 32),
+                                                           __builtin_amdgcn_mbcnt_lo((uint32_t)m[u], 0u));
+                const int at = end - __popcll(m[u]) + rank;
+                const spk_winner wn = winners[base + u * kWide + (int)threadIdx.x];
+                const int y0 = wn.y * g.stride - g.pad, x0 = wn.x * g.stride - g.pad;
+                const long long off = ((long long)bs[u] * g.Ci * g.Hi + y0) * g.Wi + x0;
+                list_at[at] = make_int4((int)off, (int)(off >> 32), y0, x0);
+                list_ra[at] = make_int4(wn.t, __float_as_int(s_rate[qs[u]][0]), __float_as_int(s_rate[qs[u]][1]),
+                                        s_stab[qs[u]]);
+            }
+        }
+        __syncthreads();
+        n_total += n;
+        // winners in batches: a batch's pre-spike loads are issued before any
+        // is used (the same winner for every lane, so its record is scalar)
+        auto pre_time = [&](int i) {
+            const int4 e = list_at[i];
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane(e.x);
+            const int hi = __builtin_amdgcn_readfirstlane(e.y);
+            const int iy = __builtin_amdgcn_readfirstlane(e.z) + ky;
+            const int ix = __builtin_amdgcn_readfirstlane(e.w) + kx;
+            const bool inside = (unsigned)iy < (unsigned)g.Hi && (unsigned)ix < (unsigned)g.Wi;
+            const uint8_t *at = in_times + (((long long)hi << 32) | lo) + rel;
+            const int t = *(inside ? at : in_times);  // (no branch around the load)
+            return inside ? t : spk::kNever;
+        };
+        auto add = [&](int i, int t_pre) {
+            const int4 e = list_ra[i];
+            const float a = t_pre <= e.x ? __int_as_float(e.y) : __int_as_float(e.z);
+            float d = a * wl;
+            d = d * wu;
+            acc = acc + (e.w ? d : a);
+        };
+        constexpr int kBatch = 16;
+        int i0 = 0;
+        for (; i0 + kBatch <= n; i0 += kBatch) {
+            int tp[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; u++) tp[u] = pre_time(i0 + u);
+#pragma unroll
+            for (int u = 0; u < kBatch; u++) add(i0 + u, tp[u]);
+        }
+        if (i0 < n) {
+            int tp[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; u++) tp[u] = pre_time(min(i0 + u, n - 1));
+#pragma unroll
+            for (int u = 0; u < kBatch; u++)
+                if (i0 + u < n) add(i0 + u, tp[u]);
+        }
+        __syncthreads();  // the list is rewritten next round
+    }
+    if (n_total == 0 || !live) return;
+    float v = w0 + acc;
+    v = fminf(U, fmaxf(L, v));
+    w[at_w] = v;
+    if (w16) {
+        __half h = __float2half_rn(v);
+        w16[at_w] = *reinterpret_cast<uint16_t *>(&h);
     }
 }
 
@@ -207,7 +368,14 @@ extern "C" spk_status spk_stdp_update(float *w, uint16_t *w_f16, int Co, int Ci,
     StdpCfgs c{};
     c.n = n_cfg;
     for (int q = 0; q < n_cfg; q++) c.c[q] = cfg[q];
-    const size_t lds = (size_t)Ci * Kh * Kw * sizeof(float);
+    const int taps = Ci * Kh * Kw;
+    if (taps > kSplitTaps) {
+        hipLaunchKernelGGL(k_stdp_wide, dim3(Co, spk::ceil_div(taps, kWide)), dim3(kWide), 0,
+                           spk::stream_of(stream), w, w_f16, in_times, winners, n_winners, winner_cfg, g, c);
+        SPK_LAUNCHED("spk_stdp_update");
+        return SPK_OK;
+    }
+    const size_t lds = (size_t)taps * sizeof(float);
     hipLaunchKernelGGL(k_stdp, dim3(Co), dim3(kThreads), lds, spk::stream_of(stream), w, w_f16,
                        in_times, winners, n_winners, winner_cfg, g, c);
     SPK_LAUNCHED("spk_stdp_update");

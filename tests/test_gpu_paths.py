@@ -55,3 +55,33 @@ def test_fc_fire_edges(B, I, O, T, theta, dens, dt, by):
         return
     exc = (np.abs(o_V.astype(np.float64) - theta) <= 1e-4 * abs(theta)).any(axis=1)
     check_fire(np_(g_tf), np_(g_vk), o_tf, o_vk, exc)
+
+
+@pytest.mark.parametrize("Co,Ci,K,B,H,k,hw", [
+    (3, 57, 3, 4, 5, 2, False),      # 513 synapses: the first size split over blocks
+    (4, 64, 3, 300, 6, 8, True),     # 2400 winner slots: a second round of the list
+    (2, 250, 5, 40, 5, 1, False),    # 6250 synapses, most winners on one map
+])
+def test_stdp_split_synapses(Co, Ci, K, B, H, k, hw):
+    dev = gpu()
+    rng = np.random.default_rng(Ci + B)
+    x = random_times(rng, (B, Ci, H, H), 15, 0.4)
+    w = rng.uniform(0.1, 0.9, size=(Co, Ci, K, K)).astype(np.float32)
+    win = np.zeros((B, k), oracle.WINNER_DTYPE)
+    for f, hi in (("c", Co), ("y", H), ("x", H), ("t", 15)):
+        win[f] = rng.integers(0, hi, size=(B, k))
+    win["c"][rng.random((B, k)) < 0.5] = Co - 1
+    n = rng.integers(0, k + 1, size=B).astype(np.int32)
+    cfgs = [(0.004, -0.003, 0.0, 1.0, 1), (-0.0005, 0.004, 0.0, 1.0, 0)]
+    wc = rng.integers(0, 2, size=(B, k)).astype(np.int32)
+    # the change of a weight is a float sum of at most B*k terms below 0.004,
+    # each rounded: small steps keep it below the weights' tolerance
+    cfgs = [(a / B, m / B, lo, up, st) for a, m, lo, up, st in cfgs]
+    wd = _t(w, dev)
+    wh = wd.half() if hw else None
+    winners = _t(win.view(np.int32).reshape(B, k, 5), dev)
+    spk.spk_stdp_update(wd, _t(x, dev), winners, _t(n, dev), cfgs, 1, K // 2, winner_cfg=_t(wc, dev), w_f16=wh)
+    ref = oracle.stdp_update(w, x, win, n, cfgs, 1, K // 2, winner_cfg=wc)
+    assert np.abs(np_(wd) - ref).max() <= W_ABS
+    if hw:
+        np.testing.assert_array_equal(np_(wh), np_(wd).astype(np.float16))
