@@ -1,8 +1,10 @@
 // spk_conv_fire: spiking convolution + integrate-and-fire (Spyker §II-E.1, Eq. 2).
 //
-// Dispatch, first match: firing layers with T <= 32 whose weights fit the
-// registers of a wave take the time-batched matrix-core kernel of
-// spk_conv_pt.hip; readout layers (theta = +inf) the split-K kernel of
+// Dispatch, first match: fully connected layers the kernel of spk_fc_fire.hip
+// (half weights, or sizes the staged kernels do not reach); spike inputs the
+// list-driven kernel of spk_conv_ls.hip (see list_driven); firing layers with
+// T <= 32 whose weights fit the registers of a wave the time-batched
+// matrix-core kernel of spk_conv_pt.hip; readout layers (theta = +inf) the split-K kernel of
 // spk_conv_fast.hip; other firing layers without dense potentials the
 // register-resident kernels of spk_conv_fast.hip; shapes the matrix-core
 // kernels of spk_conv_mfma.hip cover (the dense-potential mode among them) go
@@ -12,8 +14,9 @@
 // and records the first step whose potential exceeds theta.  Kernel o's
 // weights are staged in LDS as float.
 //
-// spk_pool_conv_fire pools (§II-E.3) inside the packing pass of the first two
-// paths, and with the spk_pool kernel in front of the others.
+// spk_pool_conv_fire pools (§II-E.3) inside the packing passes of
+// spk_conv_ls.hip, spk_conv_pt.hip and the split-K readout, and with the
+// spk_pool kernel in front of the others.
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
@@ -83,9 +86,8 @@ __global__ __launch_bounds__(kThreads) void k_conv_fire_direct(
 
 static bool is_readout(float theta, bool potentials) { return !(theta <= 3.4e38f) && !potentials; }
 
-extern "C" size_t spk_conv_fire_workspace_size(int B, int T, int Ci, int Hi, int Wi, int Co,
-                                               int Kh, int Kw, int stride, int pad, float theta,
-                                               int potentials)
+size_t spk::conv_least_workspace(int B, int T, int Ci, int Hi, int Wi, int Co, int Kh, int Kw,
+                                 int stride, int pad, float theta, int potentials)
 {
     const int Ho = spk_out_extent(Hi, Kh, stride, pad), Wo = spk_out_extent(Wi, Kw, stride, pad);
     if (B <= 0 || Ci <= 0 || Co <= 0 || Ho <= 0 || Wo <= 0) return 0;
@@ -104,6 +106,69 @@ extern "C" size_t spk_conv_fire_workspace_size(int B, int T, int Ci, int Hi, int
                                    potentials != 0))
             need = std::max(need, spk::conv_pt_workspace(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo));
     return need;
+}
+
+// Whether a layer is computed from spike lists (given the scratch for it).
+// Lists pay while less than about half of the inputs fire.  How many do is not
+// known here, but neurons that cross a threshold below a part r of their taps
+// need no more than about that part of them to fire.  Times in us, lists /
+// spk_conv_pt.hip, at the part of the inputs that fire:
+//  - half weights (spike inputs), more than 16 steps, where a position fills a
+//    32-row tile either way: 64 -> 128 maps 3x3, 64 x 32 x 32: 127 / 198 at
+//    30 %, 174 / 199 at 50 %; 48 -> 131 maps at 93 %: 77 / 49.  Where a block's
+//    table has room for 32 of the maps only, 138 / 86 at 76 %;
+//  - half weights, 9 to 16 steps, where spk_conv_pt.hip puts two positions in a
+//    tile: 64 -> 128 maps 57 / 110 at 5 %, 76 / 112 at 20 %, 105 / 112 at 40 %;
+//    the short windows of few channels gain nothing;
+//  - small layers are bound by what a wave does once, the table load above all
+//    (20 -> 60 maps, 16 x 28 x 28, 15 steps: 24 / 21);
+//  - float masters follow pooled, dense inputs (30 -> 250 maps, 15 steps: 69 / 50
+//    at 91 %) and keep the order of summation of spk_conv_pt.hip;
+//  - wherever spk_conv_pt.hip does not reach (rows too wide to stage, more than
+//    32 steps): 90 / 736 at 90 x 70 x 90, 29 / 115 with 60 steps.
+static bool list_driven(int B, int T, int Ci, int Hi, int Wi, int Co, int Kh, int Kw, int stride, int pad,
+                        int Ho, int Wo, bool half_w, bool readout, bool potentials, float theta)
+{
+    bool wide = false;
+    if (!spk::conv_ls_supported(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, half_w, readout, potentials, &wide))
+        return false;
+    const float part = theta / ((float)Ci * Kh * Kw);
+    const long long tiles = (long long)B * Ho * Wo * ((Co + 31) / 32);  // positions x 32 maps
+    if (half_w && (T > 16 ? part < (wide ? 0.2f : 0.12f) && tiles >= 16384
+                          : T > 8 && Ci >= 16 && part < 0.12f && tiles >= 65536))
+        return true;
+    return !spk::conv_pt_supported(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, half_w, readout, potentials);
+}
+
+// Scratch of a call: what it cannot do without, or what the list-driven path takes.
+static size_t full_workspace(int B, int T, int Ci, int Hi, int Wi, int Co, int Kh, int Kw, int stride, int pad,
+                             float theta, int potentials)
+{
+    size_t need = spk::conv_least_workspace(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, theta, potentials);
+    const int Ho = spk_out_extent(Hi, Kh, stride, pad), Wo = spk_out_extent(Wi, Kw, stride, pad);
+    if (B <= 0 || Ci <= 0 || Co <= 0 || Ho <= 0 || Wo <= 0) return need;
+    for (int hw = 0; hw < 2; hw++)
+        if (list_driven(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, hw != 0,
+                        is_readout(theta, potentials != 0), potentials != 0, theta))
+            need = std::max(need, spk::conv_ls_workspace(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, hw != 0));
+    return need;
+}
+
+extern "C" size_t spk_conv_fire_workspace_size(int B, int T, int Ci, int Hi, int Wi, int Co,
+                                               int Kh, int Kw, int stride, int pad, float theta,
+                                               int potentials)
+{
+    return full_workspace(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, theta, potentials);
+}
+
+// Whether one of the kernels that stage their input reaches a layer (no dense potentials).
+static bool staged_path(int B, int T, int Ci, int Hi, int Wi, int Co, int Kh, int Kw, int stride, int pad,
+                        int Ho, int Wo, bool half_w, bool readout)
+{
+    return spk::conv_pt_supported(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, half_w, readout, false) ||
+           (readout && spk::readout_fast_supported(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo)) ||
+           spk::conv_fast_supported(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, half_w, readout, false) ||
+           spk::conv_mfma_supported(Ci, Kh, Kw, Co, half_w, readout);
 }
 
 // Checks of a convolution call and the choice of its kernels.  pool: the
@@ -132,17 +197,27 @@ static spk_status conv_run(const char *what, const uint8_t *in_times, int B, int
     SPK_REQUIRE(Co <= 65535 && B <= 65535, SPK_E_SHAPE, "%s: Co or B > 65535", what);
     const bool half_w = w_dtype == SPK_F16;
     const bool readout = is_readout(theta, potentials != nullptr);
-    const size_t need = spk_conv_fire_workspace_size(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, theta,
-                                                     potentials != nullptr);
+    const size_t need = spk::conv_least_workspace(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, theta,
+                                                  potentials != nullptr);
     SPK_REQUIRE(ws_bytes >= need && (need == 0 || ws), SPK_E_WORKSPACE,
                 "%s: workspace of %zu bytes needed, %zu given", what, need, ws_bytes);
     SPK_REQUIRE_WS_ALIGNED(ws, what);
     SPK_REQUIRE((long long)B * Ho * Wo < (1LL << 31) && (long long)Ci * Hi * Wi < (1LL << 31),
                 SPK_E_SHAPE, "%s: layer too large", what);
     hipStream_t s = spk::stream_of(stream);
-    // (a pooled call's unpooled map is not the layer's input: it takes the paths below)
-    if (!pool && spk::fc_fire_supported(T, Hi, Wi, Kh, Kw, pad, readout, potentials != nullptr))
+    // (a pooled call's unpooled map is not the layer's input: it takes the paths
+    // below).  Half weights take it at every size (256 x 1125 -> 211 maps: 14 us
+    // and one launch against two), float masters only where the staged kernels
+    // do not reach, whose order of summation their results keep.
+    if (!pool && spk::fc_fire_supported(T, Hi, Wi, Kh, Kw, pad, readout, potentials != nullptr) &&
+        (half_w || !staged_path(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, half_w, readout)))
         return spk::fc_fire(in_times, B, T, Ci, w, half_w, Co, theta, readout, out_times, out_vkey, s);
+    if (ws &&
+        list_driven(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, half_w, readout, potentials != nullptr,
+                    theta) &&
+        ws_bytes >= spk::conv_ls_workspace(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, half_w))
+        return spk::conv_fire_ls(in_times, B, T, Ci, Hi, Wi, w, half_w, Co, Kh, Kw, stride, pad, Ho, Wo,
+                                 theta, out_times, out_vkey, ws, s, pool);
     if (spk::conv_pt_supported(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, half_w, readout,
                                potentials != nullptr))
         return spk::conv_fire_pt(in_times, B, T, Ci, Hi, Wi, w, half_w, Co, Kh, Kw, stride, pad, Ho, Wo,
@@ -196,7 +271,7 @@ extern "C" size_t spk_pool_conv_fire_workspace_size(int B, int T, int Ci, int H0
     const int Hi = spk_out_extent(H0, pool_kh, pool_stride, pool_pad);
     const int Wi = spk_out_extent(W0, pool_kw, pool_stride, pool_pad);
     if (B <= 0 || Ci <= 0 || Hi <= 0 || Wi <= 0) return 0;
-    const size_t conv = spk_conv_fire_workspace_size(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, theta, 0);
+    const size_t conv = full_workspace(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, theta, 0);
     // and room for the pooled map of the paths that do not pool as they pack
     return spk::align_up(conv, 256) + spk::align_up((size_t)B * Ci * Hi * Wi, 256);
 }
@@ -222,12 +297,12 @@ extern "C" spk_status spk_pool_conv_fire(const uint8_t *in_times, int B, int T, 
                 pool_kw);
     SPK_REQUIRE(((uintptr_t)packed_w & 15u) == 0u, SPK_E_ARG,
                 "spk_pool_conv_fire: packed_w not 16-byte aligned");
-    const size_t need = spk_pool_conv_fire_workspace_size(B, T, Ci, H0, W0, pool_kh, pool_kw,
-                                                          pool_stride, pool_pad, Co, Kh, Kw, stride,
-                                                          pad, theta);
+    const size_t pooled_ws = spk::align_up((size_t)B * Ci * Hi * Wi, 256);
+    const size_t need = spk::align_up(spk::conv_least_workspace(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, theta, 0), 256) + pooled_ws;
     SPK_REQUIRE(ws_bytes >= need && ws, SPK_E_WORKSPACE,
                 "spk_pool_conv_fire: workspace of %zu bytes needed, %zu given", need, ws_bytes);
-    const size_t conv_ws = need - spk::align_up((size_t)B * Ci * Hi * Wi, 256);
+    // the pooled map of the paths that write one lies at the end
+    const size_t conv_ws = (ws_bytes - pooled_ws) / 256 * 256;
     const spk::PoolIn pool{in_times, pooled_times, H0,      W0,
                            pool_kh,  pool_kw,      pool_stride, pool_pad,
                            (long long)B * Ci * H0 * W0, -1};

@@ -1,0 +1,791 @@
+// spk_conv_fire, firing layers from lists of the spikes in each window
+// (Spyker §II-E.1 Eq. 2; first-spike firing of §II-D.3 and §II-E).
+//
+// A position's potentials at every step are V[step, map] = sum over the spikes
+// of its window of [t <= step] * W[tap, map], so only the taps that fire are
+// products: the kernel gathers a window's spikes into 16-tap slices and runs
+// them through 32x32x16 products (rows: 32 steps of one position, columns: 32
+// maps), the A fragment [t <= step] built from the slice's spike times and the
+// B fragment gathered from a weight table in LDS by the slice's taps
+// (ds_read_b64_tr_b16 reads four table rows per 16 lanes and hands each lane
+// its column).  A 3x3 window over 64 channels at 5 % holds 29 spikes: 2
+// slices instead of 36.
+//
+// Operands (in the caller's workspace, written by k_pack_ls):
+//  - the spikes of each row of the padded channels-last input, in pixel order,
+//    as 32-bit entries (byte offset in the row | half 1024 + time << 16), with
+//    room for a spike of every input;
+//  - per row, the index of the first entry at or past each pixel, so the spikes
+//    of a window are one run per kernel row;
+//  - the weight table: rows in depth order (ky, kx*Cp + c, each kernel row
+//    padded to 16), per row the hi (and lo) halves of a block's maps.
+//
+// Work split: a block keeps the table of 32 or 64 maps in LDS; its waves are
+// independent after that (no barrier): each walks strips of 16 or 8
+// consecutive positions of a sample, fetching the next position's spikes while
+// one is computed, and writes a strip's results as runs of positions per map.
+//
+// What bounds it on the spike-input layer (64 -> 128 maps 3x3, 128 x 64 x 64
+// positions, 30 steps, half weights): vector issue.  A position of 64 maps
+// takes 137 vector instructions (61 of them the crossing of 64 maps x 32 steps,
+// found by halving; a compare and two selects per step were 110), 5 products
+// and 20 LDS instructions; the vector units are active 67 % of the time and
+// the matrix cores 16 %.  1,190 us with k_fire_lb (which skips only slices
+// without any spike) against 430 us at 5 %; 1.46 against 0.68 ms at 20 %.  The
+// packing pass takes 41 us (22 us for the channels-last copy alone).
+#include <type_traits>
+
+#include "spk_conv_pt.h"
+
+namespace {
+
+typedef short s4 __attribute__((ext_vector_type(4)));
+#define SPK_LDS __attribute__((address_space(3)))
+
+constexpr int kScratch = 64 * 2 + 64 * 4;  // a wave's staged spikes: 64 times (halves), 64 table offsets
+
+struct LsGeom {
+    PGeom g;
+    int PS;      // row pointers per packed row (Wp + 1, even)
+    int rows;    // table rows: SK * 16 (one zero row follows in LDS)
+    int ncb;     // map blocks
+    int SPS;     // strips per sample
+    int strips;
+};
+
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// 0x01 in each byte of x that is not zero
+__device__ __forceinline__ uint32_t nonzero4(uint32_t x)
+{
+    return ((((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) >> 7) & 0x01010101u;
+}
+
+// Bit k: byte k of the word fires (differs from T).
+__device__ __forceinline__ uint32_t fired16(uint4 v, uint32_t never4)
+{
+    const uint32_t pick = 0x08040201u;
+    uint32_t m = __builtin_amdgcn_udot4(nonzero4(v.x ^ never4), pick, 0u, false);
+    m |= __builtin_amdgcn_udot4(nonzero4(v.y ^ never4), pick, 0u, false) << 4;
+    m |= __builtin_amdgcn_udot4(nonzero4(v.z ^ never4), pick, 0u, false) << 8;
+    m |= __builtin_amdgcn_udot4(nonzero4(v.w ^ never4), pick, 0u, false) << 12;
+    return m;
+}
+
+// Blocks [0, nb_in): one padded input row each, built in LDS as bytes
+// (fill_row), whose spikes are listed: a word of 16 bytes per thread, the
+// entries in front of it by a scan of the words' counts.  The blocks after
+// them: eight maps of the weight table each.
+template <int NP, bool kHalfW, int NTB>
+__global__ __launch_bounds__(256) void k_pack_ls(const uint8_t *__restrict__ in, const void *__restrict__ wv,
+                                                 LsGeom l, int nb_in, uint8_t *__restrict__ xp,
+                                                 uint16_t *__restrict__ ptr, uint8_t *__restrict__ tbl,
+                                                 int *__restrict__ sign, spk::PoolIn pool)
+{
+    extern __shared__ __align__(16) uint8_t sm[];
+    __shared__ int tot[4];
+    const PGeom &g = l.g;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if ((int)blockIdx.x < nb_in) {
+        const int b = blockIdx.x / g.Hp, py = blockIdx.x - b * g.Hp;
+        const int iy = py - g.pad;
+        uint32_t *list = reinterpret_cast<uint32_t *>(xp + (size_t)blockIdx.x * g.pitch);
+        uint16_t *rp = ptr + (size_t)blockIdx.x * l.PS;
+        if ((unsigned)iy >= (unsigned)g.Hi) {
+            for (int e = tid; e < l.PS; e += 256) rp[e] = 0;
+            return;
+        }
+        const uint32_t never4 = 0x01010101u * (uint32_t)g.T;
+        const int nw = (g.rowb + 15) / 16;
+        for (int e = tid; e < nw; e += 256) reinterpret_cast<uint4 *>(sm)[e] = make_uint4(never4, never4, never4, never4);
+        __syncthreads();
+        fill_row(in, g, pool, b, iy, sm);
+        __syncthreads();
+        // each thread lists a run of words; the spikes in front of it by a scan
+        const int per = (nw + 255) / 256, wa = min(tid * per, nw), wb = min(wa + per, nw);
+        int n = 0;
+        for (int w = wa; w < wb; w++) n += __popc(fired16(reinterpret_cast<const uint4 *>(sm)[w], never4));
+        int scan = n;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int v = __shfl_up(scan, d);
+            if (lane >= d) scan += v;
+        }
+        if (lane == 63) tot[wave] = scan;
+        __syncthreads();
+        int at = scan - n;
+#pragma unroll
+        for (int v = 0; v < 3; v++) at += v < wave ? tot[v] : 0;
+        for (int w = wa; w < wb; w++) {
+            uint32_t m = fired16(reinterpret_cast<const uint4 *>(sm)[w], never4);
+            // pixels that start in this word
+            int px = (16 * w + g.Cp - 1) / g.Cp;
+            for (int s = px * g.Cp - 16 * w; s < 16 && px <= g.Wp; s += g.Cp, px++)
+                rp[px] = (uint16_t)(at + __popc(m & ((1u << s) - 1u)));
+            while (m) {
+                const int k = __builtin_ctz(m);
+                m &= m - 1u;
+                list[at++] = (uint32_t)(16 * w + k) | ((0x6400u | (uint32_t)sm[16 * w + k]) << 16);
+            }
+        }
+        if (tid == 255 && g.rowb == 16 * nw) rp[g.Wp] = (uint16_t)at;
+        return;
+    }
+    // table rows of maps 8*q .. +7 (virtual map (jy, jx, o) as in k_pack_pt)
+    constexpr int kMaps = 32 * NTB, kRow = NP * kMaps * 2;
+    const int ov0 = 8 * ((int)blockIdx.x - nb_in);
+    const int taps = g.Ci * g.Kh * g.Kw;
+    float *wl = reinterpret_cast<float *>(sm);
+    int neg = 0;  // some weight of these maps is negative (or NaN)
+    for (int m = 0; m < 8; m++) {
+        const int ov = ov0 + m, o = ov % g.Co;
+        for (int e = tid; e < taps; e += 256) {
+            float w = 0.0f;
+            if (ov < g.Cv) {
+                const size_t at = (size_t)o * taps + e;
+                w = kHalfW ? (float)reinterpret_cast<const _Float16 *>(wv)[at] : reinterpret_cast<const float *>(wv)[at];
+            }
+            wl[m * taps + e] = w;
+            neg |= !(w >= 0.0f);
+        }
+    }
+    neg = __syncthreads_or(neg);
+    if (tid == 0) sign[(int)blockIdx.x - nb_in] = neg;
+    uint8_t *out = tbl + (size_t)(ov0 / kMaps) * l.rows * kRow + (ov0 % kMaps) * 2;
+    for (int r = tid; r < l.rows; r += 256) {
+        const int kyv = r / (g.Q16 * 16), j = r - kyv * g.Q16 * 16;
+        const int kxv = j / g.Cp, c = j - kxv * g.Cp;
+        h8 hi, lo;
+#pragma unroll
+        for (int m = 0; m < 8; m++) {
+            const int jb = (ov0 + m) / g.Co, jy = jb / g.bx, jx = jb - jy * g.bx;
+            const int ky = kyv - jy * g.stride, kx = kxv - jx * g.stride;
+            const bool live = j < g.run && c < g.Ci && (unsigned)ky < (unsigned)g.Kh && (unsigned)kx < (unsigned)g.Kw;
+            const float w = live ? wl[m * taps + (c * g.Kh + ky) * g.Kw + kx] : 0.0f;
+            const _Float16 hw = (_Float16)w;
+            hi[m] = hw;
+            lo[m] = (_Float16)(w - (float)hw);
+        }
+        *reinterpret_cast<h8 *>(out + (size_t)r * kRow) = hi;
+        if (NP == 2) *reinterpret_cast<h8 *>(out + (size_t)r * kRow + kMaps * 2) = lo;
+    }
+}
+
+// What the kernel reads of a layer's geometry.
+struct LsArgs {
+    int T, Hp, pitch, PS, Khv, Q16, Wv, HvWv, Wp;
+    int sy, sx;       // input rows and columns from one position to the next
+    int Cp, Kwv;
+    int rows, ncb, SPS, strips, nranges;
+    int lpair;        // log2 of the table rows between 32-byte pads in LDS
+    int Co, HoWo;
+    int by, bx, Ho, Wo;  // blocked positions (by * bx > 1)
+    float theta;
+};
+
+__device__ __forceinline__ h8 tr_frag(uint32_t a, uint32_t b)
+{
+    const s4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((SPK_LDS s4 *)a);
+    const s4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((SPK_LDS s4 *)b);
+    const short v __attribute__((ext_vector_type(8))) = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+    return __builtin_bit_cast(h8, v);
+}
+
+// The first of N potentials that never fall above theta, by halving: its index
+// is added to `at`, its value returned (the last potential if none is above).
+template <int N>
+__device__ __forceinline__ float halve(const float (&v)[N], float theta, uint32_t &at)
+{
+    if constexpr (N == 1) {
+        return v[0];
+    } else {
+        float w[N / 2];
+        const bool c = v[N / 2 - 1] > theta;
+#pragma unroll
+        for (int i = 0; i < N / 2; i++) w[i] = c ? v[i] : v[i + N / 2];
+        at += c ? 0u : (uint32_t)(N / 2);
+        return halve<N / 2>(w, theta, at);
+    }
+}
+
+// First of N potentials (in step order) above theta, N if none, and its value
+// (the last potential if none).  kUp: the potentials never fall from one step
+// to the next (no weight below zero): about one select per step instead of a
+// compare and two.
+template <bool kUp, int N>
+__device__ __forceinline__ void crossing(const float (&v)[N], float theta, uint32_t &t, float &key)
+{
+    if constexpr (kUp) {
+        t = 0u;
+        key = halve<N>(v, theta, t);
+        t = key > theta ? t : (uint32_t)N;
+    } else {
+        t = (uint32_t)N;
+        key = v[N - 1];
+#pragma unroll
+        for (int i = N - 1; i >= 0; i--) {
+            const bool c = v[i] > theta;
+            t = c ? (uint32_t)i : t;
+            key = c ? v[i] : key;
+        }
+    }
+}
+
+__device__ __forceinline__ void swap32(float &a, float &b)
+{
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(p[0]);
+    b = __uint_as_float(p[1]);
+}
+__device__ __forceinline__ void swap16(float &a, float &b)
+{
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(p[0]);
+    b = __uint_as_float(p[1]);
+}
+__device__ __forceinline__ void swap32(uint32_t &a, uint32_t &b)
+{
+    const auto p = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = p[0];
+    b = p[1];
+}
+__device__ __forceinline__ void swap16(uint32_t &a, uint32_t &b)
+{
+    const auto p = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = p[0];
+    b = p[1];
+}
+
+// The tiles of a position: TP = 32 steps x 32 maps (32x32x16 products) or TP =
+// 16 steps x 16 maps (16x16x32), kMaps maps in all.
+template <int TP, int NTB>
+struct Tiles {
+    static constexpr int kN = TP == 32 ? NTB : 2 * NTB;  // tiles
+    static constexpr int kE = TP == 32 ? 16 : 4;         // elements of a lane
+    typedef float Acc __attribute__((ext_vector_type(kE)));
+    Acc acc[kN];
+
+    // Waits until the products issued so far have written the accumulators:
+    // where a loop over products is left through a branch, the compiler's copies
+    // of accumulators at the start of the next block may lack that wait.
+    __device__ __forceinline__ void settle()
+    {
+#pragma unroll
+        for (int c = 0; c < kN; c++) {
+            if (TP == 32) asm volatile("s_nop 11" : "+v"(acc[c]));
+            else asm volatile("s_nop 7" : "+v"(acc[c]));
+        }
+    }
+
+    // Step of the A fragment's row (lane % TP): a lane's elements are steps
+    // 16*(lane/32) + e (TP = 32) or 4*(lane/16) + e (TP = 16), in order.
+    static __device__ __forceinline__ int step_of_row(int lane)
+    {
+        if (TP == 16) return lane & 15;
+        const int r = lane & 31;
+        return 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3);
+    }
+
+    // Spike step (TP: none) and key potential of this lane's map: lane (64
+    // maps), lane % 32 (32 maps at TP = 32), 16*(lane/32) + lane%16 (32 maps
+    // at TP = 16).  64 maps: the tiles' lane halves (quarters) are exchanged
+    // so that a lane holds every step of one map.
+    template <bool kUp>
+    __device__ __forceinline__ void find(float theta, int lane, uint32_t &t, float &key)
+    {
+        if constexpr (TP == 32 && NTB == 2) {
+            float v[32];
+#pragma unroll
+            for (int e = 0; e < 16; e++) {
+                v[e] = acc[0][e];
+                v[16 + e] = acc[1][e];
+                swap32(v[e], v[16 + e]);
+            }
+            crossing<kUp, 32>(v, theta, t, key);
+        } else if constexpr (TP == 32) {
+            float v[16];
+#pragma unroll
+            for (int e = 0; e < 16; e++) v[e] = acc[0][e];
+            uint32_t t0;
+            float k0;
+            crossing<kUp, 16>(v, theta, t0, k0);
+            uint32_t t1 = t0;
+            float k1 = k0;
+            swap32(t0, t1);  // t0: steps 0..15's result, t1: steps 16..31's
+            swap32(k0, k1);
+            t = t0 < 16u ? t0 : 16u + t1;
+            key = t0 < 16u ? k0 : k1;
+        } else if constexpr (NTB == 2) {
+            float v[16];  // [tile, then quarter of the steps][element]
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+#pragma unroll
+                for (int c = 0; c < 4; c++) v[4 * c + e] = acc[c][e];
+                swap32(v[e], v[8 + e]);
+                swap32(v[4 + e], v[12 + e]);
+                swap16(v[e], v[4 + e]);
+                swap16(v[8 + e], v[12 + e]);
+            }
+            crossing<kUp, 16>(v, theta, t, key);
+        } else {
+            float v[4], w[4];
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                v[e] = acc[0][e];
+                w[e] = acc[1][e];
+                swap32(v[e], w[e]);  // steps 4q + e and 8 + 4q + e, q = lane/16 % 2
+            }
+            uint32_t ta, tb;
+            float ka, kb;
+            crossing<kUp, 4>(v, theta, ta, ka);
+            crossing<kUp, 4>(w, theta, tb, kb);
+            uint32_t ta1 = ta, tb1 = tb;
+            float ka1 = ka, kb1 = kb;
+            swap16(ta, ta1);  // quarters 0 and 1
+            swap16(ka, ka1);
+            swap16(tb, tb1);  // quarters 2 and 3
+            swap16(kb, kb1);
+            t = ta < 4u ? ta : (ta1 < 4u ? 4u + ta1 : (tb < 4u ? 8u + tb : 12u + tb1));
+            key = ta < 4u ? ka : (ta1 < 4u ? ka1 : (tb < 4u ? kb : kb1));
+        }
+    }
+};
+
+__device__ __forceinline__ f16v mfma(h8 a, h8 b, f16v c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
+typedef float f4v __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f4v mfma(h8 a, h8 b, f4v c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
+
+// NP: 2 = hi/lo products of float masters, 1 = half weights.  NTB: 32-map
+// columns of a block.  TP: steps of a tile.  KH: kernel rows when the
+// instance is made for them, else 0.  kBlk: positions are blocks of outputs.
+// kStrip: positions per strip.
+template <int NP, int NTB, int TP, int KH, bool kBlk, int kStrip>
+__global__ __launch_bounds__(1024) void k_fire_ls(const uint8_t *__restrict__ xp,
+                                                  const uint16_t *__restrict__ ptr,
+                                                  const uint8_t *__restrict__ tbl,
+                                                  const int *__restrict__ sign, LsArgs g,
+                                                  uint8_t *__restrict__ out_t, float *__restrict__ out_v)
+{
+    typedef Tiles<TP, NTB> Tl;
+    constexpr int kMaps = 32 * NTB, kRow = NP * kMaps * 2;
+    constexpr int kStage = kMaps * kStrip * 5;
+    constexpr int kSl = TP == 32 ? 2 : 1;       // products deep of a body of 32 spikes
+    constexpr int kKg = TP == 32 ? 2 : 4;       // lane groups along the depth
+    extern __shared__ __align__(16) uint8_t lds[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+    // block -> (map block, range); the map blocks of a range share an XCD
+    const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
+    const int cb = q % g.ncb;
+    const int range = xcd + 8 * (q / g.ncb);
+    if (range >= g.nranges) return;
+    const int s_begin = (int)((long long)range * g.strips / g.nranges);
+    const int s_end = (int)((long long)(range + 1) * g.strips / g.nranges);
+    if (s_begin >= s_end) return;
+    const int kh = KH ? KH : g.Khv;
+
+    // table row r in LDS: 32 bytes of padding after every 2^lpair rows put eight
+    // consecutive rows in different banks (a gather reads 8 or 16 rows at once)
+    auto row_at = [&](uint32_t row) -> uint32_t { return row * kRow + 32u * (row >> g.lpair); };
+    {  // the table, and one row of zeros after it
+        constexpr int kW = kRow / 16;
+        const uint4 *src = reinterpret_cast<const uint4 *>(tbl + (size_t)cb * g.rows * kRow);
+        const int n = g.rows * kW;
+#pragma unroll 4
+        for (int i = threadIdx.x; i < n; i += blockDim.x)
+            *reinterpret_cast<uint4 *>(lds + row_at(i / kW) + 16 * (i % kW)) = src[i];
+        if (threadIdx.x < kW)
+            *reinterpret_cast<uint4 *>(lds + row_at(g.rows) + 16 * threadIdx.x) = make_uint4(0u, 0u, 0u, 0u);
+    }
+    bool up = true;  // no weight of the block's maps below zero
+    for (int i = 0; i < kMaps / 8; i++) up &= sign[cb * (kMaps / 8) + i] == 0;
+    __syncthreads();
+    const uint32_t base = (uint32_t)(uintptr_t)(SPK_LDS uint8_t *)lds;
+    const uint32_t zero_row = row_at(g.rows);
+    uint8_t *mine = lds + ((row_at(g.rows) + kRow + 15) & ~15u) + wave * (kStage + kScratch);
+    float *stv = reinterpret_cast<float *>(mine);
+    uint8_t *stt = mine + kMaps * kStrip * 4;
+    uint16_t *st16 = reinterpret_cast<uint16_t *>(mine + kStage);
+    uint32_t *sr32 = reinterpret_cast<uint32_t *>(mine + kStage + 128);
+
+    const int kg = lane / (64 / kKg);  // this lane's eight taps of a slice: 8*kg ..
+    // and its part of a gathered B fragment: table row 8*kg + 4*j + k4 of the
+    // slice, four columns
+    const int k4 = (lane & 15) >> 2;
+    const uint32_t col = base + 2u * (uint32_t)((TP == 32 ? 16 * ((lane >> 4) & 1) : 0) + 4 * (lane & 3));
+    constexpr int kTileB = TP == 32 ? 64 : 32;  // bytes of a tile's columns
+    const int my_step = Tl::step_of_row(lane);
+    // a map's outputs as words of four positions (16 and 4 bytes)
+    const bool words = (g.HoWo & 3) == 0 &&
+                       ((reinterpret_cast<uintptr_t>(out_v) & 15) | (reinterpret_cast<uintptr_t>(out_t) & 3)) == 0;
+    // pointers of a window: lane 2*ky + e holds the first entry at (e = 0) or
+    // past (e = 1) the window in kernel row ky
+    const int myky = lane >> 1;
+    const uint32_t my_ptr = (uint32_t)(myky * g.PS + (lane & 1) * g.Kwv);
+    const int my_map = NTB == 2 ? lane : (TP == 32 ? lane & 31 : 16 * (lane >> 5) + (lane & 15));
+
+    for (int s = s_begin + wave; s < s_end; s += nw) {
+        const int b = s / g.SPS, p0 = (s - b * g.SPS) * kStrip;
+        const int cnt = min(kStrip, g.HvWv - p0);
+        int yf = p0 / g.Wv, xf = p0 - yf * g.Wv;  // the position whose pointers are fetched next
+        auto fetch = [&]() -> uint32_t {
+            uint32_t v = 0u;
+            const uint16_t *org = ptr + (size_t)(uint32_t)(b * g.Hp + yf * g.sy) * (uint32_t)g.PS + xf * g.sx;
+            uint32_t at = my_ptr;
+            if (kBlk) {  // (a block past the last padded row or column: zero weights there)
+                const int py = min(yf * g.sy + myky, g.Hp - 1), px = min(xf * g.sx + (lane & 1) * g.Kwv, g.Wp);
+                at = (uint32_t)((py - yf * g.sy) * g.PS + px - xf * g.sx);
+            }
+            if (myky < kh) v = org[at];
+            if (++xf == g.Wv) {
+                xf = 0;
+                yf++;
+            }
+            return v;
+        };
+        // spike 64*chunk + lane of a window (pointers pv, position (yy, xx)):
+        // the packed entry, and the table row its offset in the row counts
+        // from; n: spikes in all
+        auto entries = [&](uint32_t pv, int chunk, int yy, int xx, uint32_t &ent, int &trow, int &n) {
+            const int idx = 64 * chunk + lane;
+            const int x0c = xx * g.sx * g.Cp, py = yy * g.sy;
+            int cum = 0;
+            uint32_t at = 0u;
+            int rb = 0;
+#pragma unroll
+            for (int ky = 0; ky < kh; ky++) {
+                const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)pv, 2 * ky);
+                const uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)pv, 2 * ky + 1);
+                int py_k = py + ky;
+                if (kBlk) py_k = min(py_k, g.Hp - 1);
+                const uint32_t src = (uint32_t)(b * g.Hp + py_k) * (uint32_t)g.pitch + 4u * (a - (uint32_t)cum);
+                const bool in = idx >= cum;
+                at = in ? src : at;
+                rb = in ? ky * g.Q16 * 16 - x0c : rb;
+                cum += (int)(e - a);
+            }
+            n = cum;
+            trow = rb;
+            ent = (0x6400u | (uint32_t)spk::kNever) << 16;
+            if (idx < n) ent = *reinterpret_cast<const uint32_t *>(xp + (at + 4u * (uint32_t)idx));
+        };
+        int yc = yf, xc = xf;  // the position computed
+        uint32_t pv = fetch(), pn = cnt > 1 ? fetch() : 0u;
+        uint32_t ent;
+        int n, trow;
+        entries(pv, 0, yc, xc, ent, trow, n);
+        for (int i = 0; i < cnt; i++) {
+            uint32_t p2 = 0u;
+            if (i + 2 < cnt) p2 = fetch();
+            int yn = yc, xn = xc + 1;
+            if (xn == g.Wv) {
+                xn = 0;
+                yn++;
+            }
+            uint32_t ent2 = 0u;
+            int n2 = 0, trow2 = 0;
+            if (i + 1 < cnt) entries(pn, 0, yn, xn, ent2, trow2, n2);
+
+            uint32_t ft = spk::kNever;
+            float fv = 0.0f;
+            // (no spikes: every potential is zero)
+            if (n > 0 || g.theta < 0.0f) {
+                for (int t0 = 0; t0 < g.T; t0 += TP) {
+                    const uint32_t cbv = 0x6401u + (uint32_t)min(t0 + my_step, g.T - 1);
+                    const h2 cc = as_h2(cbv | (cbv << 16));
+                    Tl tl;
+                    // 32 staged spikes, from entry 32*h
+                    auto body = [&](int h, auto zero) {
+                        u4 tq[kSl];
+                        uint32_t ro[kSl][2];
+#pragma unroll
+                        for (int k = 0; k < kSl; k++) {
+                            const int e0 = 32 * h + 16 * k + 8 * kg;
+                            tq[k] = *reinterpret_cast<const u4 *>(st16 + e0);
+#pragma unroll
+                            for (int j = 0; j < 2; j++) ro[k][j] = col + sr32[e0 + 4 * j + k4];
+                        }
+#pragma unroll
+                        for (int k = 0; k < kSl; k++) {
+                            const h8 a = frag_upto(tq[k], cc);
+#pragma unroll
+                            for (int p = 0; p < NP; p++)
+#pragma unroll
+                                for (int c = 0; c < Tl::kN; c++) {
+                                    const int o = p * kMaps * 2 + c * kTileB;
+                                    typename Tl::Acc from = tl.acc[c];
+                                    if (decltype(zero)::value && k == 0 && p == 0) from = (typename Tl::Acc)(0.0f);
+                                    tl.acc[c] = mfma(a, tr_frag(ro[k][0] + o, ro[k][1] + o), from);
+                                }
+                        }
+                    };
+                    auto stage = [&](uint32_t ce, int ct, int left) {
+                        wave_sync();  // the spikes before are read
+                        st16[lane] = (uint16_t)(ce >> 16);
+                        sr32[lane] = lane < left ? row_at((uint32_t)(ct + (int)(ce & 0xFFFFu))) : zero_row;
+                        wave_sync();
+                    };
+                    stage(ent, trow, n);
+                    body(0, std::true_type());
+                    if (n > 32) body(1, std::false_type());
+                    if (n > 64) {
+                        uint32_t ce;
+                        int ct, nn;
+                        entries(pv, 1, yc, xc, ce, ct, nn);
+                        for (int ch = 1; 64 * ch < n; ch++) {
+                            stage(ce, ct, n - 64 * ch);
+                            if (64 * (ch + 1) < n) entries(pv, ch + 1, yc, xc, ce, ct, nn);
+                            body(0, std::false_type());
+                            if (n - 64 * ch > 32) body(1, std::false_type());
+                        }
+                        tl.settle();
+                    }
+                    uint32_t t;
+                    float v;
+                    if (up) tl.template find<true>(g.theta, lane, t, v);
+                    else tl.template find<false>(g.theta, lane, t, v);
+                    if (ft == (uint32_t)spk::kNever) {
+                        ft = t < (uint32_t)TP ? t + (uint32_t)t0 : (uint32_t)spk::kNever;
+                        fv = v;
+                    }
+                    if (t0 + TP < g.T && !__builtin_amdgcn_ballot_w64(ft == (uint32_t)spk::kNever)) break;
+                }
+            }
+            stv[my_map * kStrip + (i ^ (my_map & (kStrip - 1)))] = fv;
+            stt[my_map * kStrip + i] = (uint8_t)ft;
+            pv = pn;
+            pn = p2;
+            ent = ent2;
+            trow = trow2;
+            n = n2;
+            yc = yn;
+            xc = xn;
+        }
+        wave_sync();
+        const int m0 = cb * kMaps;
+        // (opaque to the compiler, which would otherwise keep the addresses
+        // below in registers over the whole strip)
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        float *ov = out_v + (size_t)(b * g.Co + m0) * g.HoWo;
+        uint8_t *ot = out_t + (size_t)(b * g.Co + m0) * g.HoWo;
+        if constexpr (kBlk) {
+            // virtual map (jy, jx, o); consecutive lanes on consecutive outputs
+            // of a map's row
+            const int per = kStrip * g.bx;
+            for (int e = ln; e < g.Co * g.by * per; e += 64) {
+                const int f = e / per, w = e - f * per;
+                const int o = f / g.by, jy = f - o * g.by;
+                const int blk = w / g.bx, jx = w - blk * g.bx;
+                const int p = p0 + blk, yb = p / g.Wv, xb = p - yb * g.Wv;
+                const int oy = yb * g.by + jy, ox = xb * g.bx + jx;
+                const int m = (jy * g.bx + jx) * g.Co + o;
+                if (blk < cnt && oy < g.Ho && ox < g.Wo) {
+                    const uint32_t at = (uint32_t)(o * g.HoWo + oy * g.Wo + ox);
+                    ov[at] = stv[m * kStrip + (blk ^ (m & (kStrip - 1)))];
+                    ot[at] = stt[m * kStrip + blk];
+                }
+            }
+        } else if (words) {
+            constexpr int kQ = kStrip / 4;
+            const int qd = ln % kQ;
+#pragma unroll
+            for (int k = 0; k < kMaps * kQ / 64; k++) {
+                const int m = ln / kQ + (64 / kQ) * k;
+                if (m0 + m < g.Co && 4 * qd < cnt) {
+                    const float *sv = stv + m * kStrip;
+                    const int z = m & (kStrip - 1);
+                    const uint32_t at = (uint32_t)(m * g.HoWo + p0 + 4 * qd);
+                    *reinterpret_cast<float4 *>(ov + at) = make_float4(
+                        sv[(4 * qd) ^ z], sv[(4 * qd + 1) ^ z], sv[(4 * qd + 2) ^ z], sv[(4 * qd + 3) ^ z]);
+                    *reinterpret_cast<uint32_t *>(ot + at) = *reinterpret_cast<const uint32_t *>(stt + m * kStrip + 4 * qd);
+                }
+            }
+        } else {
+            const int i = ln % kStrip;
+#pragma unroll 4
+            for (int k = 0; k < kMaps * kStrip / 64; k++) {
+                const int m = ln / kStrip + (64 / kStrip) * k;
+                if (m0 + m < g.Co && i < cnt) {
+                    const uint32_t at = (uint32_t)(m * g.HoWo + p0 + i);
+                    ov[at] = stv[m * kStrip + (i ^ (m & (kStrip - 1)))];
+                    ot[at] = stt[m * kStrip + i];
+                }
+            }
+        }
+        wave_sync();
+    }
+}
+
+constexpr size_t kLdsMax = 160 * 1024;
+
+struct Plan {
+    LsGeom l;
+    int ntb, nw;
+    int strip;        // positions per strip
+    int lpair;        // see LsArgs
+    size_t fix, per;  // LDS bytes of the table, and of a wave
+    bool ok;
+};
+
+size_t table_bytes(const LsGeom &l, int np, int ntb) { return (size_t)l.rows * np * ntb * 64; }
+size_t ls_xp_bytes(const LsGeom &l) { return spk::align_up((size_t)l.g.B * l.g.Hp * l.g.pitch, 256); }
+size_t ls_sign_bytes(const LsGeom &l, int ntb) { return spk::align_up((size_t)l.ncb * ntb * 4 * sizeof(int), 256); }
+size_t ls_ptr_bytes(const LsGeom &l) { return spk::align_up((size_t)l.g.B * l.g.Hp * l.PS * 2, 256); }
+
+Plan make_plan(int B, int T, int Ci, int Hi, int Wi, int Co, int Kh, int Kw, int stride, int pad, int Ho, int Wo,
+               bool half_w)
+{
+    Plan p{};
+    p.l.g = make_pgeom(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, half_w);
+    PGeom &g = p.l.g;
+    g.pitch = (4 * Wi * Ci + 15) / 16 * 16;
+    p.l.PS = (g.Wp + 2) & ~1;
+    p.l.rows = g.SK * 16;
+    const int np = half_w ? 1 : 2;
+    // 64 maps and 16 positions a strip when 16 waves fit beside the table; else
+    // shorter strips, then fewer waves, then 32 maps
+    for (int ntb = g.NT >= 2 ? 2 : 1; ntb >= 1 && !p.ok; ntb--) {
+        const int row = np * ntb * 64;
+        p.lpair = row == 256 ? 0 : (row == 128 ? 1 : 2);
+        const size_t fix = (size_t)(p.l.rows + 1) * row + 32 * (size_t)(p.l.rows >> p.lpair) + 16;
+        for (int strip = 16; strip >= 8; strip -= 8) {
+            const size_t per = (size_t)ntb * 32 * strip * 5 + kScratch;
+            const int nw = fix + per > kLdsMax ? 0 : (int)std::min<size_t>(16, (kLdsMax - fix) / per);
+            if (nw < (strip == 16 ? 16 : 8)) continue;
+            p.ntb = ntb;
+            p.strip = strip;
+            p.nw = nw;
+            p.fix = fix;
+            p.per = per;
+            p.ok = true;
+            break;
+        }
+    }
+    if (!p.ok) return p;
+    p.l.ncb = (g.NT + p.ntb - 1) / p.ntb;
+    p.l.SPS = (g.Hv * g.Wv + p.strip - 1) / p.strip;
+    return p;
+}
+
+bool shapes_ok(int B, int T, int Ci, int Hi, int Wi, int Co, int Kh, int Kw, int pad, int Ho, int Wo)
+{
+    const long long Hp = Hi + 2ll * pad, Wp = Wi + 2ll * pad;
+    if (T < 1 || T > SPK_MAX_T || (long long)B * Co * Ho * Wo >= (1ll << 31) || (long long)Ho * Wo > (1 << 22))
+        return false;
+    if (Wp * (Ci + 8) > 48 * 1024 || (long long)Ci * Kh * Kw * 32 > 64 * 1024) return false;
+    // lists of up to a gigabyte; row offsets and counts in 16 bits
+    if (B * Hp * (4ll * Wi * Ci + 16) > (1ll << 30)) return false;
+    // strips of every sample
+    return (long long)B * ((long long)Ho * Wo / 8 + 1) < (1ll << 31);
+}
+
+}  // namespace
+
+namespace spk {
+
+bool conv_ls_supported(int B, int T, int Ci, int Hi, int Wi, int Co, int Kh, int Kw, int stride, int pad, int Ho,
+                       int Wo, bool half_w, bool readout, bool potentials, bool *wide)
+{
+    if (readout || potentials || B < 1 || Ci < 1 || Co < 1 || Ho < 1 || Wo < 1) return false;
+    if (!shapes_ok(B, T, Ci, Hi, Wi, Co, Kh, Kw, pad, Ho, Wo)) return false;
+    const Plan p = make_plan(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, half_w);
+    if (wide) *wide = p.ntb == 2 || p.l.g.NT == 1;
+    return p.ok && p.l.g.Khv <= 32;
+}
+
+size_t conv_ls_workspace(int B, int T, int Ci, int Hi, int Wi, int Co, int Kh, int Kw, int stride, int pad, int Ho,
+                         int Wo, bool half_w)
+{
+    const Plan p = make_plan(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, half_w);
+    return ls_xp_bytes(p.l) + ls_ptr_bytes(p.l) + ls_sign_bytes(p.l, p.ntb) +
+           p.l.ncb * table_bytes(p.l, half_w ? 1 : 2, p.ntb);
+}
+
+namespace {
+
+template <int NP, int NTB, int TP, int KH, bool kBlk, int kStrip>
+void launch_ls(dim3 grid, int nw, size_t lds, hipStream_t s, const uint8_t *xp, const uint16_t *ptr,
+               const uint8_t *tbl, const int *sign, const LsArgs &a, uint8_t *out_t, float *out_v)
+{
+    auto kern = k_fire_ls<NP, NTB, TP, KH, kBlk, kStrip>;
+    static const bool attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 (int)kLdsMax) == hipSuccess;
+    (void)attr;
+    hipLaunchKernelGGL(kern, grid, dim3(64 * nw), lds, s, xp, ptr, tbl, sign, a, out_t, out_v);
+}
+
+template <int NP, bool kHalfW, int NTB>
+spk_status run_ls(const Plan &p, const uint8_t *in, const void *w, float theta, uint8_t *out_t, float *out_v, void *ws,
+                  hipStream_t s, const PoolIn &pool, size_t pack_lds)
+{
+    const LsGeom &l = p.l;
+    const PGeom &g = l.g;
+    uint8_t *xp = reinterpret_cast<uint8_t *>(ws);
+    uint16_t *ptr = reinterpret_cast<uint16_t *>(xp + ls_xp_bytes(l));
+    int *sign = reinterpret_cast<int *>(xp + ls_xp_bytes(l) + ls_ptr_bytes(l));
+    uint8_t *tbl = reinterpret_cast<uint8_t *>(sign) + ls_sign_bytes(l, NTB);
+    const int nb_in = g.B * g.Hp;
+    hipLaunchKernelGGL((k_pack_ls<NP, kHalfW, NTB>), dim3(nb_in + l.ncb * NTB * 4), dim3(256), pack_lds, s, in, w, l,
+                       nb_in, xp, ptr, tbl, sign, pool);
+    SPK_LAUNCHED("spk_conv_fire");
+    // one block per CU; two of 12 waves when two tables fit (77 registers, six
+    // waves a SIMD; the 64-map blocks of 32 steps need 99: five).  Few strips:
+    // fewer waves per block, but four to load the table.
+    int blocks = 1, nw = p.nw;
+    if ((NTB == 1 || g.T <= 16) && 2 * (p.fix + 12 * p.per) <= kLdsMax) {
+        blocks = 2;
+        nw = 12;
+    }
+    int nr = std::max(1, blocks * cu_count() / l.ncb);
+    const int per = (l.strips + nr - 1) / nr;
+    if (per < nw) nr = std::min(nr, (l.strips + per - 1) / per);
+    else nr = std::min(nr, (l.strips + nw - 1) / nw);
+    nw = std::min(nw, std::max(4, per));
+    const size_t lds = p.fix + (size_t)nw * p.per;
+    const LsArgs a{g.T, g.Hp, g.pitch, l.PS, g.Khv, g.Q16, g.Wv, g.Hv * g.Wv, g.Wp, g.by * g.stride, g.bx * g.stride,
+                   g.Cp, g.Kwv, l.rows, l.ncb, l.SPS, l.strips, nr, p.lpair, g.Co, g.Ho * g.Wo, g.by, g.bx, g.Ho, g.Wo, theta};
+    const dim3 grid(8 * l.ncb * ((nr + 7) / 8));
+    auto pick = [&](auto strip) {
+        constexpr int S = decltype(strip)::value;
+        constexpr bool kMay = NTB == 1;  // blocked positions have at most 32 virtual maps
+        const bool k3 = g.Khv == 3;
+        if (kMay && g.by * g.bx > 1)
+            return g.T <= 16 ? launch_ls<NP, NTB, 16, 0, kMay, S> : launch_ls<NP, NTB, 32, 0, kMay, S>;
+        if (g.Khv == 5) return g.T <= 16 ? launch_ls<NP, NTB, 16, 5, false, S> : launch_ls<NP, NTB, 32, 5, false, S>;
+        if (g.T <= 16) return k3 ? launch_ls<NP, NTB, 16, 3, false, S> : launch_ls<NP, NTB, 16, 0, false, S>;
+        return k3 ? launch_ls<NP, NTB, 32, 3, false, S> : launch_ls<NP, NTB, 32, 0, false, S>;
+    };
+    const auto launch = p.strip == 16 ? pick(std::integral_constant<int, 16>()) : pick(std::integral_constant<int, 8>());
+    launch(grid, nw, lds, s, xp, ptr, tbl, sign, a, out_t, out_v);
+    return check_launch("spk_conv_fire");
+}
+
+}  // namespace
+
+spk_status conv_fire_ls(const uint8_t *in, int B, int T, int Ci, int Hi, int Wi, const void *w, bool half_w, int Co,
+                        int Kh, int Kw, int stride, int pad, int Ho, int Wo, float theta, uint8_t *out_t,
+                        float *out_v, void *ws, hipStream_t s, const PoolIn *pool)
+{
+    Plan p = make_plan(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, half_w);
+    p.l.strips = B * p.l.SPS;
+    PoolIn pl = pool ? *pool : PoolIn{};
+    pl.stage = -1;
+    const size_t row = align_up((size_t)p.l.g.rowb, 16);
+    if (pool && row + pool_stage_bytes(pl, Ci) <= 64 * 1024) pl.stage = (int)row;
+    const size_t pack_lds = std::max<size_t>((size_t)Ci * Kh * Kw * 32,
+                                             row + (pl.stage >= 0 ? pool_stage_bytes(pl, Ci) : 0));
+    if (half_w)
+        return p.ntb == 2 ? run_ls<1, true, 2>(p, in, w, theta, out_t, out_v, ws, s, pl, pack_lds)
+                          : run_ls<1, true, 1>(p, in, w, theta, out_t, out_v, ws, s, pl, pack_lds);
+    return p.ntb == 2 ? run_ls<2, false, 2>(p, in, w, theta, out_t, out_v, ws, s, pl, pack_lds)
+                      : run_ls<2, false, 1>(p, in, w, theta, out_t, out_v, ws, s, pl, pack_lds);
+}
+
+}  // namespace spk

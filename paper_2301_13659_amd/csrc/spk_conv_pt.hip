@@ -36,675 +36,9 @@
 // of them fires).  Results go through LDS so that each map's run of positions
 // is written with coalesced stores.  In a sparse group, the 16-tap slices in
 // which no input of the tile fires are skipped.
-#include <hip/hip_fp16.h>
-
-#include <algorithm>
-#include <map>
-#include <mutex>
-#include <tuple>
-
-#include "spk_internal.h"
+#include "spk_conv_pt.h"
 
 namespace {
-
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-typedef float f16v __attribute__((ext_vector_type(16)));
-typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-
-constexpr int kThreads = 256;
-constexpr int kG = 64;                         // positions per group
-constexpr int kStageStride = kG + 1;           // staged results: [map][position], padded
-constexpr int kRange = 16 * 1024;              // Xp bytes of a group's input rows (at most)
-constexpr int kSlackPT = 64;                   // readable bytes past the end of Xp
-constexpr uint32_t kSelLo = 0x04010400u;       // bytes 0,1 -> halves 1024 + b
-constexpr uint32_t kSelHi = 0x04030402u;       // bytes 2,3 -> halves 1024 + b
-
-// LDS: [staged V x 2 | staged t x 2 | position table x 3 | word counts per
-// wave | fire flag per 16 input bytes | input as halves (2 bytes per input
-// byte, sized per launch to the largest group's range, so small images leave
-// room for more blocks)]
-constexpr size_t kStvOff = 0;
-constexpr size_t kSttOff = kStvOff + 2 * 32 * kStageStride * sizeof(float);
-constexpr size_t kTabOff = (kSttOff + 2 * 32 * kStageStride + 15) / 16 * 16;
-constexpr size_t kTabBytes = 3 * kG * 3 * sizeof(int);
-constexpr size_t kCntOff = kTabOff + kTabBytes;
-constexpr size_t kFlagOff = kCntOff + 2 * (kThreads / 64) * sizeof(int);
-constexpr size_t kHalOff = (kFlagOff + kRange / 16 + 15) / 16 * 16;
-
-// Layers with few maps take their output positions in blocks of by x bx
-// (1 x 1 otherwise): a tile's 32 columns are then (position of the block,
-// map) pairs, so four maps fill a tile with 2 x 4 positions instead of
-// leaving 28 of its 32 columns empty.  A block is one position of a virtual
-// layer with by*bx*Co maps, a window of Khv x Kwv input pixels (the union of
-// its positions' windows) and strides by*stride, bx*stride; the weight of
-// virtual map (jy, jx, o) at virtual tap (c, kyv, kxv) is W[o, c, kyv -
-// jy*stride, kxv - jx*stride] inside the real window and 0 outside it.
-struct PGeom {
-    int B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo;
-    int by, bx;    // output positions per block
-    int Hv, Wv;    // blocks: ceil(Ho / by) x ceil(Wo / bx)
-    int Khv, Kwv;  // input window of a block
-    int Cv;        // virtual maps: by * bx * Co
-    int Cp;    // channels per padded pixel of Xp
-    int Hp, Wp;
-    int rowb;  // Wp * Cp: bytes of one padded input row
-    int slack; // readable bytes past the last padded row
-    int run;   // Kwv * Cp: taps of one kernel row
-    int Q16;   // ceil(run / 16): 16-tap slices per kernel row
-    int SK;    // Khv * Q16: slices of the layer
-    int SKp;   // slices of the kernel instance (>= SK; the extra ones are zero)
-    int P;     // B * Hv * Wv blocks (positions when the blocks are 1 x 1)
-    int NT;    // ceil(Cv / 32)
-    int hw;    // input words (16 bytes) the LDS halves of a launch hold
-    int TP;    // steps per position in a tile: 8, 16 or 32
-    int lgTP;
-};
-
-int choose_cp(int Ci, int Kw)
-{
-    const int c8 = (Ci + 7) / 8 * 8;
-    return (Kw * c8 + 15) / 16 == (Kw * Ci + 15) / 16 ? c8 : Ci;
-}
-
-PGeom make_pgeom_blocked(int B, int T, int Ci, int Hi, int Wi, int Co, int Kh, int Kw, int stride,
-                         int pad, int Ho, int Wo, int by, int bx)
-{
-    PGeom g{};
-    g.B = B; g.T = T; g.Ci = Ci; g.Hi = Hi; g.Wi = Wi; g.Co = Co; g.Kh = Kh; g.Kw = Kw;
-    g.stride = stride; g.pad = pad; g.Ho = Ho; g.Wo = Wo;
-    g.by = by; g.bx = bx;
-    g.Hv = (Ho + by - 1) / by;
-    g.Wv = (Wo + bx - 1) / bx;
-    g.Khv = (by - 1) * stride + Kh;
-    g.Kwv = (bx - 1) * stride + Kw;
-    g.Cv = by * bx * Co;
-    g.Cp = choose_cp(Ci, g.Kwv);
-    g.Hp = Hi + 2 * pad;
-    g.Wp = Wi + 2 * pad;
-    g.rowb = g.Wp * g.Cp;
-    // a block past the last row or column reads up to by*stride rows and a
-    // row's width beyond the padded input (only for its positions that are
-    // past the output, whose weights there are zero)
-    g.slack = kSlackPT + (by > 1 || bx > 1 ? (by * stride + 1) * g.rowb : 0);
-    g.run = g.Kwv * g.Cp;
-    g.Q16 = (g.run + 15) / 16;
-    g.SK = g.Khv * g.Q16;
-    g.SKp = g.SK;
-    g.P = B * g.Hv * g.Wv;
-    g.NT = (g.Cv + 31) / 32;
-    g.TP = T <= 8 ? 8 : (T <= 16 ? 16 : 32);
-    g.lgTP = T <= 8 ? 3 : (T <= 16 ? 4 : 5);
-    return g;
-}
-
-// Geometry of a layer: 1 x 1 blocks, or for layers of at most 16 maps the
-// block shape with the least work (slices x blocks x column tiles) among
-// those that fill at most 32 columns and whose slices still fit the
-// in-register kernels (18 with float weights, 36 with half weights), when it
-// saves at least a fifth of the work.
-PGeom make_pgeom(int B, int T, int Ci, int Hi, int Wi, int Co, int Kh, int Kw, int stride, int pad,
-                 int Ho, int Wo, bool half_w)
-{
-    const PGeom one = make_pgeom_blocked(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, 1, 1);
-    if (Co > 16) return one;
-    static const int kShapes[][2] = {{1, 2}, {2, 1}, {2, 2}, {1, 4}, {4, 1}, {2, 4},
-                                     {4, 2}, {4, 4}, {2, 8}, {8, 2}, {4, 8}, {8, 4}};
-    const int limit = half_w ? 36 : 18;
-    const long long base = (long long)one.SK * one.NT * one.P;
-    PGeom best = one;
-    long long best_work = base;
-    for (const auto &sh : kShapes) {
-        if (sh[0] * sh[1] * Co > 32 || sh[0] > Ho || sh[1] > Wo) continue;
-        const PGeom g = make_pgeom_blocked(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, sh[0], sh[1]);
-        if (g.SK > limit) continue;
-        const long long work = (long long)g.SK * g.NT * g.P;
-        if (work < best_work) {
-            best = g;
-            best_work = work;
-        }
-    }
-    return best_work * 5 <= base * 4 ? best : one;
-}
-
-// Alignment of every window run in the staged halves: 16, 8, 4 or 2 bytes.
-int read_mode(int Cp) { return Cp % 8 == 0 ? 3 : (Cp % 4 == 0 ? 2 : (Cp % 2 == 0 ? 1 : 0)); }
-
-size_t xp_bytes(const PGeom &g) { return spk::align_up((size_t)g.B * g.Hp * g.rowb + g.slack, 256); }
-size_t bp_bytes(const PGeom &g, int np) { return (size_t)g.NT * g.SKp * np * 64 * sizeof(h8); }
-
-__device__ __forceinline__ h2 as_h2(uint32_t u) { return __builtin_bit_cast(h2, u); }
-__device__ __forceinline__ uint32_t as_u(h2 h) { return __builtin_bit_cast(uint32_t, h); }
-
-// [t <= last] for two staged halves 1024 + t (c = 1025 + last in both):
-// c - (1024 + t) is a small exact integer, >= 1 iff t <= last; clamp to [0, 1].
-__device__ __forceinline__ uint32_t upto2(uint32_t x, h2 c)
-{
-    const h2 one = {(_Float16)1.0f, (_Float16)1.0f}, zero = {(_Float16)0.0f, (_Float16)0.0f};
-    h2 a = c - as_h2(x);
-    return as_u(__builtin_elementwise_min(__builtin_elementwise_max(a, zero), one));
-}
-
-__device__ __forceinline__ h8 frag_upto(u4 x, h2 c)
-{
-    u4 v = {upto2(x[0], c), upto2(x[1], c), upto2(x[2], c), upto2(x[3], c)};
-    return __builtin_bit_cast(h8, v);
-}
-
-// 8 staged halves (16 bytes) at byte offset at from base (16-aligned); kMode
-// gives the alignment every window run has: 3 = 16, 2 = 8, 1 = 4, 0 = 2 bytes.
-template <int kMode>
-__device__ __forceinline__ u4 lds_read16(const uint8_t *base, int at)
-{
-    if (kMode == 3) return *reinterpret_cast<const u4 *>(base + at);
-    if (kMode == 2) {
-        const uint2 a = *reinterpret_cast<const uint2 *>(base + at);
-        const uint2 b = *reinterpret_cast<const uint2 *>(base + at + 8);
-        return u4{a.x, a.y, b.x, b.y};
-    }
-    if (kMode == 1) {
-        const uint32_t *w = reinterpret_cast<const uint32_t *>(base + at);
-        return u4{w[0], w[1], w[2], w[3]};
-    }
-    const uint32_t *w = reinterpret_cast<const uint32_t *>(base + (at & ~3));
-    const uint32_t w0 = w[0], w1 = w[1], w2 = w[2], w3 = w[3], w4 = w[4];
-    const uint32_t sh = (uint32_t)(at & 3);
-    return u4{__builtin_amdgcn_alignbyte(w1, w0, sh), __builtin_amdgcn_alignbyte(w2, w1, sh),
-              __builtin_amdgcn_alignbyte(w3, w2, sh), __builtin_amdgcn_alignbyte(w4, w3, sh)};
-}
-
-// Padded input rows [r0, r1) hold the windows of output positions [p0, p1].
-__host__ __device__ inline void group_rows(const PGeom &g, int p0, int p1, int &r0, int &r1)
-{
-    const int HvWv = g.Hv * g.Wv;
-    const int b0 = p0 / HvWv, y0 = (p0 - b0 * HvWv) / g.Wv;
-    const int b1 = p1 / HvWv, y1 = (p1 - b1 * HvWv) / g.Wv;
-    r0 = b0 * g.Hp + y0 * g.by * g.stride;
-    r1 = b1 * g.Hp + y1 * g.by * g.stride + g.Khv;
-}
-
-// ------------------------------------------------------------------ packing
-
-// Blocks [0, nb_in): one padded input row (b, py) each, transposed through
-// LDS from channel rows to channels-last, times clamped to T (a pooled input
-// row is pooled there from the staged window rows); the last of them fills
-// the readable slack.  A pooled input whose rows are too wide to stage runs a
-// grid-stride pass over the Xp bytes instead, each pooling its window from
-// the unpooled map.  Blocks [nb_in, nb_in + 32*NT): one map o each
-// (maps past Co are zero), written as B fragments: lane l holds map o (l % 32)
-// and taps 8*(l/32)..+7 of a slice.
-template <int NP, bool kHalfW>
-__global__ __launch_bounds__(256) void k_pack_pt(const uint8_t *__restrict__ in,
-                                                 const void *__restrict__ wv, PGeom g, int nb_in,
-                                                 uint8_t *__restrict__ xp, h8 *__restrict__ bp,
-                                                 spk::PoolIn pool)
-{
-    extern __shared__ __align__(16) uint8_t sm[];
-    const uint8_t never = (uint8_t)g.T;
-    if ((int)blockIdx.x < nb_in && pool.src && pool.stage < 0) {
-        // pooled input too wide to stage: each thread writes Xp bytes
-        // (b, py, px, c), the pooling window read from the unpooled map; the
-        // Xp body is below 2^30 bytes
-        const uint32_t body = (uint32_t)g.B * g.Hp * g.rowb, total = body + (uint32_t)g.slack;
-        for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (uint32_t)nb_in * blockDim.x) {
-            uint32_t v = never;
-            if (e < body) {
-                const uint32_t rowi = e / (uint32_t)g.rowb, within = e - rowi * (uint32_t)g.rowb;
-                const int b = (int)(rowi / (uint32_t)g.Hp), py = (int)(rowi - (uint32_t)b * g.Hp);
-                const int px = (int)(within / (uint32_t)g.Cp), c = (int)within - px * g.Cp;
-                const int iy = py - g.pad, ix = px - g.pad;
-                if ((unsigned)iy < (unsigned)g.Hi && (unsigned)ix < (unsigned)g.Wi && c < g.Ci) {
-                    const long long plane = (long long)b * g.Ci + c;
-                    const uint32_t t = spk::pool_cell(pool, plane, iy, ix);
-                    if (pool.pooled) pool.pooled[(plane * g.Hi + iy) * g.Wi + ix] = (uint8_t)t;
-                    v = min(t, (uint32_t)never);
-                }
-            }
-            xp[e] = (uint8_t)v;
-        }
-        return;
-    }
-    if ((int)blockIdx.x < nb_in) {
-        const int b = blockIdx.x / g.Hp, py = blockIdx.x - b * g.Hp;
-        const int iy = py - g.pad;
-        uint8_t *row = xp + ((size_t)b * g.Hp + py) * g.rowb;
-        // rows of a multiple of 16 bytes start 16-byte aligned: 16-byte fills and stores
-        const bool wide = (g.rowb & 15) == 0;
-        const uint4 never16 = make_uint4(0x01010101u * never, 0x01010101u * never, 0x01010101u * never,
-                                         0x01010101u * never);
-        if ((unsigned)iy < (unsigned)g.Hi) {
-            if (wide) {
-                for (int e = threadIdx.x; e < g.rowb / 16; e += blockDim.x) reinterpret_cast<uint4 *>(sm)[e] = never16;
-            } else {
-                for (int e = threadIdx.x; e < g.rowb; e += blockDim.x) sm[e] = never;
-            }
-            __syncthreads();
-            auto put = [&](int c, int x, uint8_t v) { sm[(x + g.pad) * g.Cp + c] = v < never ? v : never; };
-            if (pool.src) {
-                // the input row is pooled here (and kept when asked for)
-                spk::pool_row(pool, (long long)b * g.Ci, g.Ci, g.Hi, g.Wi, iy,
-                              reinterpret_cast<uint32_t *>(sm + pool.stage), put);
-            } else {
-                const uint8_t *src = in + (size_t)b * g.Ci * g.Hi * g.Wi + (size_t)iy * g.Wi;
-                const size_t plane = (size_t)g.Hi * g.Wi;
-                if ((g.Wi & 3) == 0 && (plane & 3) == 0 && (((uintptr_t)src) & 3) == 0 && (g.Ci & 3) == 0 &&
-                    (g.Cp & 3) == 0) {
-                    // 4 channels x 4 pixels per thread: four dword loads (one per channel),
-                    // times clamped to T byte-wise, a byte transpose to four dwords of 4
-                    // channels each, written to LDS as dwords
-                    const int wq = g.Wi >> 2, cq = g.Ci >> 2, n16 = cq * wq;
-                    const uint32_t t4 = 0x01010101u * never;
-                    for (int e = threadIdx.x; e < n16; e += blockDim.x) {
-                        const int x4 = e % wq, c4 = e / wq;
-                        uint32_t d[4];
-#pragma unroll
-                        for (int k = 0; k < 4; k++)
-                            d[k] = *reinterpret_cast<const uint32_t *>(src + (4 * c4 + k) * plane + 4 * x4);
-#pragma unroll
-                        for (int k = 0; k < 4; k++) {
-                            // bytes above T (T <= 32) become T: a byte is above T when its
-                            // top bit is set or its low 7 bits plus 127 - T carry into it
-                            const uint32_t gt =
-                                (((d[k] & 0x7f7f7f7fu) + 0x01010101u * (uint32_t)(127 - (int)never)) | d[k]) &
-                                0x80808080u;
-                            const uint32_t full = (gt >> 7) * 0xFFu;
-                            d[k] = (d[k] & ~full) | (t4 & full);
-                        }
-                        const uint32_t t0 = __builtin_amdgcn_perm(d[1], d[0], 0x05010400u);
-                        const uint32_t t1 = __builtin_amdgcn_perm(d[3], d[2], 0x05010400u);
-                        const uint32_t t2 = __builtin_amdgcn_perm(d[1], d[0], 0x07030602u);
-                        const uint32_t t3 = __builtin_amdgcn_perm(d[3], d[2], 0x07030602u);
-                        const uint32_t o[4] = {__builtin_amdgcn_perm(t1, t0, 0x05040100u),
-                                               __builtin_amdgcn_perm(t1, t0, 0x07060302u),
-                                               __builtin_amdgcn_perm(t3, t2, 0x05040100u),
-                                               __builtin_amdgcn_perm(t3, t2, 0x07060302u)};
-#pragma unroll
-                        for (int q = 0; q < 4; q++)
-                            *reinterpret_cast<uint32_t *>(sm + (4 * x4 + q + g.pad) * g.Cp + 4 * c4) = o[q];
-                    }
-                } else if ((g.Wi & 3) == 0 && (plane & 3) == 0 && (((uintptr_t)src) & 3) == 0) {
-                    // the row of every channel as dwords, all of a thread's loads in flight first
-                    const int wq = g.Wi >> 2, n4 = g.Ci * wq;
-                    for (int e0 = threadIdx.x; e0 < n4; e0 += 8 * (int)blockDim.x) {
-                        uint32_t v[8];
-#pragma unroll
-                        for (int u = 0; u < 8; u++) {
-                            const int e = min(e0 + u * (int)blockDim.x, n4 - 1);
-                            const int c = e / wq, x4 = e - c * wq;
-                            v[u] = *reinterpret_cast<const uint32_t *>(src + c * plane + 4 * x4);
-                        }
-#pragma unroll
-                        for (int u = 0; u < 8; u++) {
-                            const int e = e0 + u * (int)blockDim.x;
-                            if (e >= n4) break;
-                            const int c = e / wq, x4 = e - c * wq;
-#pragma unroll
-                            for (int q = 0; q < 4; q++) put(c, 4 * x4 + q, (uint8_t)(v[u] >> (8 * q)));
-                        }
-                    }
-                } else {
-                    const int n = g.Ci * g.Wi;
-                    for (int e = threadIdx.x; e < n; e += blockDim.x) {
-                        const int c = e / g.Wi, x = e - c * g.Wi;
-                        put(c, x, src[(size_t)c * plane + x]);
-                    }
-                }
-            }
-            __syncthreads();
-            if (wide) {
-                for (int e = threadIdx.x; e < g.rowb / 16; e += blockDim.x)
-                    reinterpret_cast<uint4 *>(row)[e] = reinterpret_cast<const uint4 *>(sm)[e];
-            } else {
-                for (int e = threadIdx.x; e < g.rowb; e += blockDim.x) row[e] = sm[e];
-            }
-        } else if (wide) {
-            for (int e = threadIdx.x; e < g.rowb / 16; e += blockDim.x) reinterpret_cast<uint4 *>(row)[e] = never16;
-        } else {
-            for (int e = threadIdx.x; e < g.rowb; e += blockDim.x) row[e] = never;
-        }
-        if ((int)blockIdx.x == nb_in - 1)
-            for (int e = threadIdx.x; e < g.slack; e += blockDim.x) row[g.rowb + e] = never;
-        return;
-    }
-    // virtual map ov = (jy*bx + jx)*Co + o: real map o of block position (jy, jx)
-    const int ov = blockIdx.x - nb_in;
-    const int jb = ov / g.Co, o = ov - jb * g.Co;
-    const int jy = jb / g.bx, jx = jb - jy * g.bx;
-    const int taps = g.Ci * g.Kh * g.Kw;
-    float *wl = reinterpret_cast<float *>(sm);
-    const bool real = ov < g.Cv;
-    for (int e = threadIdx.x; e < taps; e += blockDim.x) {
-        float w = 0.0f;
-        if (real) {
-            const size_t at = (size_t)o * taps + e;
-            w = kHalfW ? (float)reinterpret_cast<const _Float16 *>(wv)[at]
-                       : reinterpret_cast<const float *>(wv)[at];
-        }
-        wl[e] = w;
-    }
-    __syncthreads();
-    const int nt = ov / 32, col = ov & 31;
-    for (int f = threadIdx.x; f < g.SKp * 2; f += blockDim.x) {
-        const int s = f >> 1, half = f & 1;
-        const int kyv = s / g.Q16, jq = s - kyv * g.Q16;
-        const int ky = kyv - jy * g.stride;
-        h8 hi, lo;
-        // addresses first (padding taps read word 0), then the reads together:
-        // no branch around a read
-        int at[8];
-        bool live[8];
-#pragma unroll
-        for (int e = 0; e < 8; e++) {
-            const int j = jq * 16 + half * 8 + e;
-            const int kxv = j / g.Cp, c = j - kxv * g.Cp;
-            const int kx = kxv - jx * g.stride;
-            live[e] = s < g.SK && j < g.run && c < g.Ci && (unsigned)ky < (unsigned)g.Kh &&
-                      (unsigned)kx < (unsigned)g.Kw;
-            at[e] = live[e] ? (c * g.Kh + ky) * g.Kw + kx : 0;
-        }
-        float wv8[8];
-#pragma unroll
-        for (int e = 0; e < 8; e++) wv8[e] = wl[at[e]];
-#pragma unroll
-        for (int e = 0; e < 8; e++) {
-            const float w = live[e] ? wv8[e] : 0.0f;
-            const _Float16 hw = (_Float16)w;
-            hi[e] = hw;
-            lo[e] = (_Float16)(w - (float)hw);
-        }
-        const size_t ts = (size_t)nt * g.SKp + s;
-        const int lane = col + 32 * half;
-        bp[(ts * NP) * 64 + lane] = hi;
-        if (NP == 2) bp[(ts * NP + 1) * 64 + lane] = lo;
-    }
-}
-
-// -------------------------------------------------------------------- firing
-
-struct Tab {
-    int xoff;   // Xp offset of the block's window origin
-    int obase;  // output offset of its first position for map 0: b*Co*Ho*Wo + y0*Wo + x0
-    int yx;     // y0 << 16 | x0, its first position
-};
-
-// Per-group position table (threads 0..kG-1; slots past the group repeat its last).
-__device__ __forceinline__ void fill_table(const PGeom &g, int gs, int cnt, Tab *tab)
-{
-    const int i = threadIdx.x;
-    if (i < kG) {
-        const int p = gs + min(i, cnt - 1);
-        const int HvWv = g.Hv * g.Wv;
-        const int b = p / HvWv, rem = p - b * HvWv;
-        const int yb = rem / g.Wv, xb = rem - yb * g.Wv;
-        const int y0 = yb * g.by, x0 = xb * g.bx;
-        Tab t;
-        t.xoff = (b * g.Hp + y0 * g.stride) * g.rowb + x0 * g.stride * g.Cp;
-        t.obase = b * g.Co * g.Ho * g.Wo + y0 * g.Wo + x0;
-        t.yx = (y0 << 16) | x0;
-        tab[i] = t;
-    }
-}
-
-// The Xp bytes [a0, a1 + 32) (a0 16-aligned) as 16-byte words, PF per
-// thread of a block of NTH (word threadIdx.x + NTH*i); words past the end of
-// Xp read its last.
-template <int NTH = kThreads>
-struct Staged {
-    static constexpr int PF = (kRange / 16 + NTH - 1) / NTH;
-    uint4 w[PF];
-};
-
-__device__ __forceinline__ int range_words(int a0, int a1) { return (a1 - a0 + 32 + 15) / 16; }
-
-template <int NTH = kThreads>
-__device__ __forceinline__ Staged<NTH> load_range(const uint8_t *xp, size_t xp_words, int a0, int a1)
-{
-    Staged<NTH> st;
-    const size_t w0 = (size_t)a0 / 16;
-    const int nw = range_words(a0, a1);
-#pragma unroll
-    for (int i = 0; i < Staged<NTH>::PF; i++) {
-        const int k = (int)threadIdx.x + NTH * i;
-        if (NTH * i < nw) {  // words past the range are neither loaded nor stored
-            size_t w = w0 + (size_t)min(k, nw - 1);
-            w = w < xp_words ? w : xp_words - 1;
-            st.w[i] = reinterpret_cast<const uint4 *>(xp)[w];
-        }
-    }
-    return st;
-}
-
-// Staged words to LDS as halves 1024 + t, plus a flag per word: does any of
-// its 16 times fire within the window (clamped times: any byte below T)?
-// Each wave also records in cnt how many of its words are flagged, for
-// group_sparse.
-template <int NTH>
-__device__ __forceinline__ void store_range(const Staged<NTH> &st, uint8_t *hal, uint8_t *flags, int *cnt,
-                                            uint32_t never4, int nw, int hw)
-{
-    int flagged = 0, words = 0;
-#pragma unroll
-    for (int i = 0; i < Staged<NTH>::PF; i++) {
-        const int k = (int)threadIdx.x + NTH * i;
-        if (NTH * i >= nw) break;
-        const uint4 v = st.w[i];
-        const u4 lo = {__builtin_amdgcn_perm(0x64646464u, v.x, kSelLo), __builtin_amdgcn_perm(0x64646464u, v.x, kSelHi),
-                       __builtin_amdgcn_perm(0x64646464u, v.y, kSelLo), __builtin_amdgcn_perm(0x64646464u, v.y, kSelHi)};
-        const u4 hi = {__builtin_amdgcn_perm(0x64646464u, v.z, kSelLo), __builtin_amdgcn_perm(0x64646464u, v.z, kSelHi),
-                       __builtin_amdgcn_perm(0x64646464u, v.w, kSelLo), __builtin_amdgcn_perm(0x64646464u, v.w, kSelHi)};
-        if (k < hw) {
-            reinterpret_cast<u4 *>(hal)[2 * k] = lo;
-            reinterpret_cast<u4 *>(hal)[2 * k + 1] = hi;
-        }
-        const bool f = ((v.x ^ never4) | (v.y ^ never4) | (v.z ^ never4) | (v.w ^ never4)) != 0u;
-        if (k < kRange / 16) flags[k] = f ? 1 : 0;  // (larger blocks have threads past the flag bytes)
-        flagged += __builtin_popcountll(__builtin_amdgcn_ballot_w64(f && k < nw));
-        words += __builtin_popcountll(__builtin_amdgcn_ballot_w64(k < nw));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        cnt[2 * (threadIdx.x >> 6)] = flagged;
-        cnt[2 * (threadIdx.x >> 6) + 1] = words;
-    }
-}
-
-// Whether the staged group is sparse enough to test slices in, the same for
-// every wave of the block (from the counts store_range left; call after the
-// barrier that follows it).  A tile's slice can be skipped only when none of
-// the tile's words under it fires, so with a fraction u of the words
-// unflagged about u^pt of the slices are skipped, pt being the words a slice
-// of the tile covers (one per position when window runs are 16-byte aligned,
-// two otherwise); testing pays when that is above min_skip (below it the
-// tests cost more than the skipped products save: 40 % for k_fire_pt, 15 %
-// for k_fire_lb, where a skipped slice saves two products).  One decision for
-// the block keeps its waves equally loaded between barriers.
-template <int NW = kThreads / 64>
-__device__ __forceinline__ bool group_sparse(const int *cnt, int pt, float min_skip)
-{
-    int flagged = 0, words = 0;
-#pragma unroll
-    for (int w = 0; w < NW; w++) {
-        flagged += cnt[2 * w];
-        words += cnt[2 * w + 1];
-    }
-    const float u = words > 0 ? (float)(words - flagged) / (float)words : 0.0f;
-    float skip = u;
-    for (int i = 1; i < pt; i++) skip *= u;
-    return skip > min_skip;
-}
-
-// Staged results of positions [gs, min(gs + 64, p_end)) to the outputs,
-// consecutive threads on consecutive positions of one map.  Unblocked
-// layouts: a thread takes four consecutive positions of two maps, each
-// written with one 16-byte and one 4-byte store where the four are
-// contiguous in the output.  Blocked layouts: a thread takes one position of
-// eight maps, all its staged values read before the stores.
-__device__ __forceinline__ void write_out(const PGeom &g, int nt, int gs, int p_end, const Tab *tab,
-                                          const float *stv, const uint8_t *stt,
-                                          uint8_t *__restrict__ out_t, float *__restrict__ out_v)
-{
-    constexpr int kPer = 32 * kG / kThreads;  // maps per thread
-    constexpr int kMapStep = kThreads / kG;
-    const int HoWo = g.Ho * g.Wo;
-    const int cnt = min(p_end, gs + kG) - gs;
-    const bool blocked = g.by * g.bx > 1;
-    // (output bases aligned for the word stores: 16 bytes for V, 4 for t)
-    const bool aligned = ((reinterpret_cast<uintptr_t>(out_v) & 15) | (reinterpret_cast<uintptr_t>(out_t) & 3)) == 0;
-    if (!blocked && (HoWo & 3) == 0) {
-        // four consecutive positions of a map per thread, stored as one
-        // 16-byte V word and one 4-byte time word when they are contiguous
-        // and aligned in the output
-        constexpr int kQ = kG / 4, kMaps = kThreads / kQ;
-        const int p4 = 4 * (threadIdx.x % kQ), oc0 = threadIdx.x / kQ;
-        if (p4 >= cnt) return;
-        const Tab t0 = tab[p4];
-        const int n3 = tab[min(p4 + 3, kG - 1)].obase;
-        const bool vec = p4 + 3 < cnt && n3 == t0.obase + 3 && (t0.obase & 3) == 0 && aligned;
-#pragma unroll
-        for (int j = 0; j < 32 / kMaps; j++) {
-            const int oc = oc0 + kMaps * j, ov = nt * 32 + oc;
-            if (ov >= g.Cv) continue;
-            const float *sv = stv + oc * kStageStride + p4;
-            const uint8_t *st = stt + oc * kStageStride + p4;
-            if (vec) {
-                const float4 v4 = make_float4(sv[0], sv[1], sv[2], sv[3]);
-                const uint32_t tw = (uint32_t)st[0] | ((uint32_t)st[1] << 8) | ((uint32_t)st[2] << 16) |
-                                    ((uint32_t)st[3] << 24);
-                const int n = t0.obase + ov * HoWo;
-                *reinterpret_cast<float4 *>(out_v + n) = v4;
-                *reinterpret_cast<uint32_t *>(out_t + n) = tw;
-            } else {
-                for (int i = 0; i < 4 && p4 + i < cnt; i++) {
-                    const int n = tab[p4 + i].obase + ov * HoWo;
-                    out_v[n] = sv[i];
-                    out_t[n] = st[i];
-                }
-            }
-        }
-        return;
-    }
-    const int pi = threadIdx.x & (kG - 1), oc0 = threadIdx.x / kG;
-    if (pi >= cnt) return;
-    const Tab tb = tab[pi];
-    float v[kPer];
-    uint8_t t[kPer];
-#pragma unroll
-    for (int j = 0; j < kPer; j++) {
-        const int oc = oc0 + kMapStep * j;
-        v[j] = stv[oc * kStageStride + pi];
-        t[j] = stt[oc * kStageStride + pi];
-    }
-#pragma unroll
-    for (int j = 0; j < kPer; j++) {
-        const int ov = nt * 32 + oc0 + kMapStep * j;
-        if (ov >= g.Cv) continue;
-        int n;
-        if (blocked) {  // virtual map (jy*bx + jx)*Co + o
-            const int jb = ov / g.Co, o = ov - jb * g.Co;
-            const int jy = jb / g.bx, jx = jb - jy * g.bx;
-            if ((tb.yx >> 16) + jy >= g.Ho || (tb.yx & 0xffff) + jx >= g.Wo) continue;
-            n = tb.obase + o * HoWo + jy * g.Wo + jx;
-        } else {
-            n = tb.obase + ov * HoWo;
-        }
-        out_v[n] = v[j];
-        out_t[n] = t[j];
-    }
-}
-
-// Rows of a tile: output element e of a lane in wave half hh is row
-// 8*(e/4) + 4*hh + e%4.  The A fragment of row r is given the position slot
-// and step below.  TP = 16 and 8: each lane's elements are whole runs of
-// steps in order (TP = 16, slot hh, element e = step e; TP = 8, slot hh for
-// e < 8 and 2 + hh for e >= 8, step e % 8), so no lane needs the other half's
-// results.  TP = 32: step r, the two halves' elements interleaved.
-__device__ __forceinline__ void row_slot_step(int r, int lgTP, int &pl, int &tt)
-{
-    const int hi = r >> 3, half = (r >> 2) & 1, lo = r & 3;
-    if (lgTP == 3) {
-        pl = 2 * (hi >> 1) + half;
-        tt = ((hi & 1) << 2) | lo;
-    } else if (lgTP == 4) {
-        pl = half;
-        tt = (hi << 2) | lo;
-    } else {
-        pl = 0;
-        tt = r;
-    }
-}
-
-// Merge the two wave halves of one position slot (ft: step or NEVER; last:
-// the potential at step T-1, meaningful in the upper half only).  Each swap
-// leaves both halves' values in every lane; min and sum do not depend on
-// their order.
-__device__ __forceinline__ void merge_halves(uint32_t ft, float fv, float last, int hh, uint32_t &tf,
-                                             float &vk)
-{
-    const auto t2 = __builtin_amdgcn_permlane32_swap(ft, ft, false, false);
-    const uint32_t fb = __builtin_bit_cast(uint32_t, fv);
-    const auto v2 = __builtin_amdgcn_permlane32_swap(fb, fb, false, false);
-    const uint32_t lb = __builtin_bit_cast(uint32_t, hh ? last : 0.0f);
-    const auto l2 = __builtin_amdgcn_permlane32_swap(lb, lb, false, false);
-    const uint32_t t0 = t2[0], t1 = t2[1];
-    const float f0 = __builtin_bit_cast(float, (uint32_t)v2[0]);
-    const float f1 = __builtin_bit_cast(float, (uint32_t)v2[1]);
-    const float vl = __builtin_bit_cast(float, (uint32_t)l2[0]) + __builtin_bit_cast(float, (uint32_t)l2[1]);
-    tf = min(t0, t1);
-    const float fsel = t0 < t1 ? f0 : f1;
-    vk = tf < (uint32_t)spk::kNever ? fsel : vl;
-}
-
-// First element in [e0, e0 + n) above theta (as an offset) and its value;
-// n when there is none.
-__device__ __forceinline__ void first_above(const f16v &acc, int e0, int n, float theta, int &fe, float &fv)
-{
-    fe = n;
-    fv = 0.0f;
-#pragma unroll
-    for (int e = 15; e >= 0; e--) {
-        if (e < e0 || e >= e0 + n) continue;
-        const bool c = acc[e] > theta;
-        fe = c ? e - e0 : fe;
-        fv = c ? acc[e] : fv;
-    }
-}
-
-// Epilogue of a tile with TP steps per position (rows past T - 1 repeat step
-// T - 1, so the last element of a run is the potential at T - 1): the spike
-// time (or NEVER) and key potential of each position slot this lane holds,
-// for its map lane % 32.  TP = 8: slots hh and 2 + hh (st/sv[0], [1]); TP =
-// 16: slot hh; TP = 32: the one slot, the two wave halves merged, in every
-// lane.
-template <int TP>
-__device__ __forceinline__ void tile_epilogue(const f16v &acc, float theta, int hh, uint32_t *st, float *sv)
-{
-    if constexpr (TP == 8 || TP == 16) {
-#pragma unroll
-        for (int k = 0; k < 16 / TP; k++) {
-            int fe;
-            float fv;
-            first_above(acc, k * TP, TP, theta, fe, fv);
-            st[k] = fe < TP ? (uint32_t)fe : (uint32_t)spk::kNever;
-            sv[k] = fe < TP ? fv : acc[k * TP + TP - 1];
-        }
-    } else {
-        // the first element above theta and its step (row 8*(e/4) + 4*hh +
-        // e%4), then the minimum over the two halves through lane swaps
-        int fe;
-        float fv;
-        first_above(acc, 0, 16, theta, fe, fv);
-        const uint32_t ft = fe < 16 ? (uint32_t)(((fe >> 2) << 3) + 4 * hh + (fe & 3)) : (uint32_t)spk::kNever;
-        const float last = acc[15];  // row 31: step T - 1, in the upper half
-        merge_halves(ft, fv, last, hh, st[0], sv[0]);
-    }
-}
-
-// Position slots of the tile a lane stores (see tile_epilogue): count and
-// slot of entry k.
-__device__ __forceinline__ int slots_held(int lgTP, int hh)
-{
-    return lgTP == 3 ? 2 : (lgTP == 4 ? 1 : (hh == 0 ? 1 : 0));
-}
-__device__ __forceinline__ int slot_of(int lgTP, int hh, int k) { return lgTP == 3 ? 2 * k + hh : (lgTP == 4 ? hh : 0); }
 
 // SK: slices of the instance (all in registers), NP: 2 = hi/lo products of a
 // float master, 1 = half weights; kMode: alignment of the window runs; QC:
@@ -1637,20 +971,6 @@ int max_rows(const PGeom &g, int nranges)
     if (memo.size() > 4096) memo.clear();
     memo[key] = best;
     return best;
-}
-
-int cu_count()
-{
-    static int n = 0;
-    if (n == 0) {
-        int dev = 0, v = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
-            n = v;
-        else
-            n = 256;
-    }
-    return n;
 }
 
 int n_ranges(const PGeom &g)

@@ -141,6 +141,21 @@ spk_status conv_fire_pt(const uint8_t *in, int B, int T, int Ci, int Hi, int Wi,
                         bool half_w, int Co, int Kh, int Kw, int stride, int pad, int Ho, int Wo,
                         float theta, uint8_t *out_t, float *out_v, void *ws, hipStream_t s,
                         const PoolIn *pool = nullptr);
+// Firing layers from lists of the spikes in each window, whose weight table
+// fits a CU's LDS (spk_conv_ls.hip); pool as for conv_fire_pt.  wide
+// (nullable): set when a block takes all maps, or 64 at a time.
+bool conv_ls_supported(int B, int T, int Ci, int Hi, int Wi, int Co, int Kh, int Kw, int stride,
+                       int pad, int Ho, int Wo, bool half_w, bool readout, bool potentials, bool *wide);
+size_t conv_ls_workspace(int B, int T, int Ci, int Hi, int Wi, int Co, int Kh, int Kw, int stride,
+                         int pad, int Ho, int Wo, bool half_w);
+spk_status conv_fire_ls(const uint8_t *in, int B, int T, int Ci, int Hi, int Wi, const void *w,
+                        bool half_w, int Co, int Kh, int Kw, int stride, int pad, int Ho, int Wo,
+                        float theta, uint8_t *out_t, float *out_v, void *ws, hipStream_t s,
+                        const PoolIn *pool);
+// The scratch a convolution call cannot do without (a larger workspace opens
+// the list-driven path to more layers; see spk_conv_fire_workspace_size).
+size_t conv_least_workspace(int B, int T, int Ci, int Hi, int Wi, int Co, int Kh, int Kw, int stride,
+                            int pad, float theta, int potentials);
 // Fully connected layers (1 x 1 kernels on a 1 x 1 image): readouts, and
 // firing layers with T <= 32, in one launch without scratch (spk_fc_fire.hip).
 bool fc_fire_supported(int T, int Hi, int Wi, int Kh, int Kw, int pad, bool readout, bool potentials);

@@ -58,8 +58,8 @@ extern "C" spk_status spk_conv_fire_noalloc(const uint8_t *in_times, int B, int 
     spk::clear_error();
     // the size check needs only the shapes: a call that cannot fit launches
     // nothing and touches no device state
-    const size_t need = spk_conv_fire_workspace_size(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, theta,
-                                                     potentials != nullptr);
+    const size_t need = spk::conv_least_workspace(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, theta,
+                                                  potentials != nullptr);
     SPK_REQUIRE(need <= kScratchBytes, SPK_E_WORKSPACE,
                 "spk_conv_fire_noalloc: this layer needs %zu bytes of scratch, more than the static "
                 "%zu; use spk_conv_fire with a workspace",
@@ -70,5 +70,5 @@ extern "C" spk_status spk_conv_fire_noalloc(const uint8_t *in_times, int B, int 
         if (st != SPK_OK) return st;
     }
     return spk_conv_fire(in_times, B, T, Ci, Hi, Wi, w, w_dtype, Co, Kh, Kw, stride, pad, theta,
-                         out_times, out_vkey, potentials, ws, need, stream);
+                         out_times, out_vkey, potentials, ws, need > 0 ? kScratchBytes : 0, stream);
 }

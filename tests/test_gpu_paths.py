@@ -85,3 +85,40 @@ def test_stdp_split_synapses(Co, Ci, K, B, H, k, hw):
     assert np.abs(np_(wd) - ref).max() <= W_ABS
     if hw:
         np.testing.assert_array_equal(np_(wh), np_(wd).astype(np.float16))
+
+
+# list-driven firing: B, Ci, Hi, Wi, Co, K, stride, pad, T, theta / taps, density, dtype, signed.
+# Weights are multiples of 2^-11 (half) or 2^-12 (float, both halves of the
+# split in use) whose sums stay below 2^11: exact in any order, so every
+# output equals the oracle's bit for bit (theta lies off the grid).
+LS_CASES = [
+    (1, 16, 1, 1, 17, 1, 1, 0, 1, 0.01, 1.0, "f16", False),     # one position, one step
+    (2, 33, 7, 9, 20, 3, 1, 1, 40, 0.05, 0.4, "f32", False),    # T = 40: two windows of 32 steps; unaligned channels
+    (1, 8, 5, 7, 40, 3, 1, 1, 254, 0.1, 0.5, "f32", True),      # the longest T, potentials that fall again
+    (2, 64, 7, 9, 70, 3, 1, 1, 30, 0.08, 1.0, "f16", False),    # every input fires: nine chunks of spikes
+    (2, 64, 7, 9, 70, 3, 1, 1, 30, 0.02, 0.05, "f16", True),
+    (3, 16, 9, 11, 33, 5, 2, 2, 16, 0.02, 0.6, "f32", False),   # early end, stride 2, odd output width
+    (2, 64, 7, 7, 20, 4, 1, 1, 8, 0.01, 1.0, "f16", False),     # early end after more than one chunk
+    (2, 100, 6, 6, 40, 3, 1, 1, 15, 0.006, 0.8, "f32", False),  # a table of 32 maps a block
+    (2, 6, 23, 31, 4, 5, 1, 2, 20, 0.1, 0.4, "f32", False),     # four maps: blocks of positions
+    (2, 90, 10, 96, 24, 3, 1, 1, 12, 0.3, 0.3, "f16", False),   # rows too wide for the staged kernels
+    (40, 20, 12, 12, 64, 3, 1, 1, 20, 0.05, 0.1, "f32", False),  # many strips: several a wave
+]
+
+
+@pytest.mark.parametrize("case", LS_CASES)
+def test_list_driven_fire(case):
+    dev = gpu()
+    B, Ci, Hi, Wi, Co, K, s, p, T, part, dens, dt, signed = case
+    rng = np.random.default_rng(Ci * 100 + Co + T)
+    t = random_times(rng, (B, Ci, Hi, Wi), T, dens)
+    bits = 11 if dt == "f16" else 12
+    w = (np.round(rng.uniform(0.5, 0.999, size=(Co, Ci, K, K)) * 2 ** bits) / 2 ** bits).astype(np.float32)
+    if signed:
+        w -= np.float32(0.625)
+    theta = round(part * Ci * K * K) + 2.0 ** -14
+    wd = _t(w, dev).half() if dt == "f16" else _t(w, dev)
+    g_tf, g_vk = spk.spk_conv_fire(_t(t, dev), wd, T, s, p, theta)
+    o_tf, o_vk = oracle.conv_fire(t, w, T, s, p, theta)[:2]
+    np.testing.assert_array_equal(np_(g_tf), o_tf)
+    np.testing.assert_array_equal(np_(g_vk), o_vk)
