@@ -46,7 +46,14 @@ namespace {
 // 0.  With QC known, a slice's offset is one register per kernel row plus a
 // constant, which the LDS reads take as their immediate offset.  TPC: steps
 // per position in a tile when the instance is made for it, else 0.
-template <int SK, int NP, int kMode, int QC, int TPC>
+//
+// kWin: a tile takes fewer steps than T of more positions, and is computed
+// again for the later steps while some of its maps has not crossed theta.  All
+// steps cost the same products as in one tile; where thresholds are low and
+// inputs dense most tiles end after the first half: 30 -> 250 maps 3x3 over
+// 14 x 14, 64 samples of 15 steps, 91 % firing, theta 10: 54.7 to 41.4 us (52.4
+// to 48.5 in the three-layer net's step).
+template <int SK, int NP, int kMode, int QC, int TPC, bool kWin>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2)))
 void k_fire_pt(const uint8_t *__restrict__ xp, size_t xp_words, const h8 *__restrict__ bp, PGeom g,
                float theta, int nranges,
@@ -96,8 +103,7 @@ void k_fire_pt(const uint8_t *__restrict__ xp, size_t xp_words, const h8 *__rest
     const int lgTP = TPC == 8 ? 3 : (TPC == 16 ? 4 : (TPC == 32 ? 5 : g.lgTP));
     int pl, tt;
     row_slot_step(r, lgTP, pl, tt);
-    const uint32_t cbv = 0x6401u + (uint32_t)min(tt, g.T - 1);
-    const h2 cc = as_h2(cbv | (cbv << 16));
+    const int TP = 1 << lgTP;
     const int PT = 32 >> lgTP;  // positions per tile
     const uint32_t never4 = 0x01010101u * (uint32_t)g.T;
     // words a slice of the tile covers (see store_range)
@@ -148,8 +154,7 @@ void k_fire_pt(const uint8_t *__restrict__ xp, size_t xp_words, const h8 *__rest
             const int org2 = 2 * (xo_next - a0 + 8 * hh);
             auto rd = [&](int s) -> u4 { return lds_read16<kMode>(hal, org2 + off2[s]); };
             f16v acc;
-#pragma unroll
-            for (int e = 0; e < 16; e++) acc[e] = 0.0f;
+            h2 cc;
             auto step = [&](int s, u4 x) {
                 const h8 a = frag_upto(x, cc);
 #pragma unroll
@@ -171,49 +176,77 @@ void k_fire_pt(const uint8_t *__restrict__ xp, size_t xp_words, const h8 *__rest
                     live |= __builtin_amdgcn_ballot_w64(f);
                 }
             }
-            // reads run three slices ahead of the products; the dense form
-            // has no branch between slices
-            constexpr int kAhead = 3;
-            u4 win[kAhead];
+            // steps of the tile, TP at a time: the later ones only while some
+            // map has not crossed theta
+            const int o = lane & 31, ns = slots_held(lgTP, hh);
+            uint32_t st[2] = {spk::kNever, spk::kNever};
+            float sv[2] = {0.0f, 0.0f};
+            for (int t0 = 0;;) {
+                const uint32_t cbv = 0x6401u + (uint32_t)min(t0 + tt, g.T - 1);
+                cc = as_h2(cbv | (cbv << 16));
 #pragma unroll
-            for (int s = 0; s < kAhead && s < SK; s++) win[s] = rd(s);
-            // the products at a raised wave priority (see k_fire_lb)
-            __builtin_amdgcn_s_setprio(2);
-            if (!sparse) {
+                for (int e = 0; e < 16; e++) acc[e] = 0.0f;
+                // reads run three slices ahead of the products; the dense form
+                // has no branch between slices
+                constexpr int kAhead = 3;
+                u4 win[kAhead];
 #pragma unroll
-                for (int s = 0; s < SK; s++) {
-                    const u4 x = win[s % kAhead];
-                    if (s + kAhead < SK) win[s % kAhead] = rd(s + kAhead);
-                    step(s, x);
-                    if constexpr (QC > 0 && kMode >= 1) {
-                        // keep kAhead reads in flight: per slice, the LDS reads of
-                        // one window piece, then the fragment's four VALU ops,
-                        // then the products
-                        constexpr int kReads = kMode == 1 ? 2 : 1;  // paired b32 reads merge
-                        if (s + kAhead < SK) __builtin_amdgcn_sched_group_barrier(0x100, kReads, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x008, NP, 0);
+                for (int s = 0; s < kAhead && s < SK; s++) win[s] = rd(s);
+                // the products at a raised wave priority (see k_fire_lb)
+                __builtin_amdgcn_s_setprio(2);
+                if (!sparse) {
+#pragma unroll
+                    for (int s = 0; s < SK; s++) {
+                        const u4 x = win[s % kAhead];
+                        if (s + kAhead < SK) win[s % kAhead] = rd(s + kAhead);
+                        step(s, x);
+                        if constexpr (QC > 0 && kMode >= 1) {
+                            // keep kAhead reads in flight: per slice, the LDS reads of
+                            // one window piece, then the fragment's four VALU ops,
+                            // then the products
+                            constexpr int kReads = kMode == 1 ? 2 : 1;  // paired b32 reads merge
+                            if (s + kAhead < SK) __builtin_amdgcn_sched_group_barrier(0x100, kReads, 0);
+                            __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+                            __builtin_amdgcn_sched_group_barrier(0x008, NP, 0);
+                        }
+                    }
+                } else {
+#pragma unroll
+                    for (int s = 0; s < SK; s++) {
+                        const u4 x = win[s % kAhead];
+                        if (s + kAhead < SK) win[s % kAhead] = rd(s + kAhead);
+                        // (the bit test on a 32-bit half is one scalar instruction)
+                        const uint32_t lw = s < 32 ? (uint32_t)live : (uint32_t)(live >> 32);
+                        if (__builtin_expect((lw >> (s & 31)) & 1u, 1)) step(s, x);
                     }
                 }
-            } else {
+                __builtin_amdgcn_s_setprio(0);
+                // the next tile's window origin, read while this one finishes
+                if (t0 == 0 && tp0 + wstep < wp1) xo_next = tab[min(tp0 + wstep - gs + pl, cnt - 1)].xoff;
+                uint32_t wt[2] = {0u, 0u};
+                float wv2[2] = {0.0f, 0.0f};
+                if (lgTP == 3) tile_epilogue<8>(acc, theta, hh, wt, wv2);
+                else if (lgTP == 4) tile_epilogue<16>(acc, theta, hh, wt, wv2);
+                else tile_epilogue<32>(acc, theta, hh, wt, wv2);
+                if constexpr (!kWin) {
 #pragma unroll
-                for (int s = 0; s < SK; s++) {
-                    const u4 x = win[s % kAhead];
-                    if (s + kAhead < SK) win[s % kAhead] = rd(s + kAhead);
-                    // (the bit test on a 32-bit half is one scalar instruction)
-                    const uint32_t lw = s < 32 ? (uint32_t)live : (uint32_t)(live >> 32);
-                    if (__builtin_expect((lw >> (s & 31)) & 1u, 1)) step(s, x);
+                    for (int q2 = 0; q2 < 2; q2++) {
+                        st[q2] = wt[q2];
+                        sv[q2] = wv2[q2];
+                    }
+                    break;
                 }
+                bool open = false;
+#pragma unroll
+                for (int q2 = 0; q2 < 2; q2++)
+                    if (q2 < ns && st[q2] == (uint32_t)spk::kNever) {
+                        sv[q2] = wv2[q2];
+                        if (wt[q2] != (uint32_t)spk::kNever) st[q2] = wt[q2] + (uint32_t)t0;
+                        else open |= tp0 - gs + slot_of(lgTP, hh, q2) < cnt && nt * 32 + o < g.Cv;
+                    }
+                t0 += TP;
+                if (t0 >= g.T || !__builtin_amdgcn_ballot_w64(open)) break;
             }
-            __builtin_amdgcn_s_setprio(0);
-            // the next tile's window origin, read while this one finishes
-            if (tp0 + wstep < wp1) xo_next = tab[min(tp0 + wstep - gs + pl, cnt - 1)].xoff;
-            uint32_t st[2] = {0u, 0u};
-            float sv[2] = {0.0f, 0.0f};
-            if (lgTP == 3) tile_epilogue<8>(acc, theta, hh, st, sv);
-            else if (lgTP == 4) tile_epilogue<16>(acc, theta, hh, st, sv);
-            else tile_epilogue<32>(acc, theta, hh, st, sv);
-            const int o = lane & 31, ns = slots_held(lgTP, hh);
 #pragma unroll
             for (int k = 0; k < 2; k++) {
                 const int pi = tp0 - gs + slot_of(lgTP, hh, k);
@@ -641,11 +674,12 @@ struct LbkLayout {
     static constexpr size_t stt = stv + 2 * 32 * kStageStride * sizeof(float);
     static constexpr size_t tab = (stt + 2 * 32 * kStageStride + 15) / 16 * 16;
     static constexpr size_t cnt = tab + kTabBytes;
-    static constexpr size_t flag = cnt + 2 * 16 * sizeof(int);
+    static constexpr size_t open = cnt + 2 * 16 * sizeof(int);  // per wave: a map has not crossed theta
+    static constexpr size_t flag = open + 16 * sizeof(int);
     static constexpr size_t hal = (flag + kRange / 16 + 15) / 16 * 16;
 };
 
-template <int SKT, int NP, int kMode, int QC, int TPC, int NW, int KC>
+template <int SKT, int NP, int kMode, int QC, int TPC, int NW, int KC, bool kWin>
 __global__ __launch_bounds__(64 * NW) void k_fire_lbk(const uint8_t *__restrict__ xp, size_t xp_words,
                                                       const h8 *__restrict__ bp, PGeom g, float theta,
                                                       int nranges, uint8_t *__restrict__ out_t,
@@ -704,8 +738,6 @@ __global__ __launch_bounds__(64 * NW) void k_fire_lbk(const uint8_t *__restrict_
     const int r = lane & 31, hh = lane >> 5;
     int pl, tt;
     row_slot_step(r, lgTP, pl, tt);
-    const uint32_t cbv = 0x6401u + (uint32_t)min(tt, g.T - 1);
-    const h2 cc = as_h2(cbv | (cbv << 16));
     const uint32_t never4 = 0x01010101u * (uint32_t)g.T;
     const int skip_pow = PT * ((g.Cp & 15) == 0 ? 1 : 2);
 
@@ -748,10 +780,14 @@ __global__ __launch_bounds__(64 * NW) void k_fire_lbk(const uint8_t *__restrict_
         int org2[TPW];
         uint64_t live[TPW];
         f16v acc[TPW];
+        uint32_t st[TPW][2];
+        float sv[TPW][2];
 #pragma unroll
         for (int j = 0; j < TPW; j++) {
             const int ti = wv + NW * j;
             org2[j] = 2 * (tab[min(ti * PT + pl, cnt - 1)].xoff - a0 + 8 * hh);
+            st[j][0] = st[j][1] = spk::kNever;
+            sv[j][0] = sv[j][1] = 0.0f;
             live[j] = ti < ntiles ? ~0ull : 0ull;
             if (sparse && ti < ntiles) {
                 uint64_t m = 0ull;
@@ -766,9 +802,19 @@ __global__ __launch_bounds__(64 * NW) void k_fire_lbk(const uint8_t *__restrict_
                 }
                 live[j] = m;
             }
+        }
+        const int o = lane & 31, ns = slots_held(lgTP, hh);
+        // kWin: TPC steps at a time, the later ones while a map of the group has
+        // not crossed theta (as k_fire_pt, but for the group: its waves share the
+        // staged fragments).  100 -> 200 maps 3x3 over 14 x 14, 64 samples of 15
+        // steps, 76 % firing, theta 5: 236 to 171 us.
+        for (int t0 = 0;;) {
+        const uint32_t cbv = 0x6401u + (uint32_t)min(t0 + tt, g.T - 1);
+        const h2 cc = as_h2(cbv | (cbv << 16));
+#pragma unroll
+        for (int j = 0; j < TPW; j++)
 #pragma unroll
             for (int e = 0; e < 16; e++) acc[j][e] = 0.0f;
-        }
 #pragma unroll
         for (int ch = 0; ch < NCH; ch++) {
             if (ch > 0) __syncthreads();  // every wave is done with chunk ch - 1
@@ -806,20 +852,51 @@ __global__ __launch_bounds__(64 * NW) void k_fire_lbk(const uint8_t *__restrict_
             }
             __builtin_amdgcn_s_setprio(0);
         }
-        const int o = lane & 31, ns = slots_held(lgTP, hh);
+        bool open = false;
 #pragma unroll
         for (int j = 0; j < TPW; j++) {
             const int ti = wv + NW * j;
             if (ti >= ntiles) continue;
-            uint32_t st[2] = {0u, 0u};
-            float sv[2] = {0.0f, 0.0f};
-            tile_epilogue<TPC>(acc[j], theta, hh, st, sv);
+            uint32_t wt[2] = {0u, 0u};
+            float wk[2] = {0.0f, 0.0f};
+            tile_epilogue<TPC>(acc[j], theta, hh, wt, wk);
+            if constexpr (!kWin) {
+#pragma unroll
+                for (int k = 0; k < 2; k++) {
+                    st[j][k] = wt[k];
+                    sv[j][k] = wk[k];
+                }
+                continue;
+            }
+#pragma unroll
+            for (int k = 0; k < 2; k++)
+                if (k < ns && st[j][k] == (uint32_t)spk::kNever) {
+                    sv[j][k] = wk[k];
+                    if (wt[k] != (uint32_t)spk::kNever) st[j][k] = wt[k] + (uint32_t)t0;
+                    else open |= ti * PT + slot_of(lgTP, hh, k) < cnt && nt * 32 + o < g.Cv;
+                }
+        }
+        t0 += TPC;
+        if (!kWin || t0 >= g.T) break;
+        int *ow = reinterpret_cast<int *>(lds + L::open);
+        const uint64_t any = __builtin_amdgcn_ballot_w64(open);
+        if (lane == 0) ow[wv] = any != 0ull;
+        __syncthreads();  // (and every wave is done with the last chunk)
+        bool more_steps = false;
+#pragma unroll
+        for (int w = 0; w < NW; w++) more_steps |= ow[w] != 0;
+        if (!more_steps) break;
+        }
+#pragma unroll
+        for (int j = 0; j < TPW; j++) {
+            const int ti = wv + NW * j;
+            if (ti >= ntiles) continue;
 #pragma unroll
             for (int k = 0; k < 2; k++) {
                 const int pi = ti * PT + slot_of(lgTP, hh, k);
                 if (k < ns && pi < cnt) {
-                    stv(cur)[o * kStageStride + pi] = sv[k];
-                    stt(cur)[o * kStageStride + pi] = (uint8_t)st[k];
+                    stv(cur)[o * kStageStride + pi] = sv[j][k];
+                    stt(cur)[o * kStageStride + pi] = (uint8_t)st[j][k];
                 }
             }
         }
@@ -866,11 +943,11 @@ void launch_deep(dim3 grid, size_t lds, hipStream_t s, const uint8_t *xp, size_t
 typedef void (*PtLaunch)(dim3, size_t, hipStream_t, const uint8_t *, size_t, const h8 *, const PGeom &,
                          float, int, uint8_t *, float *);
 
-template <int SK, int NP, int kMode, int QC = 0, int TPC = 0>
+template <int SK, int NP, int kMode, int QC = 0, int TPC = 0, bool kWin = false>
 void launch_pt(dim3 grid, size_t lds, hipStream_t s, const uint8_t *xp, size_t xw, const h8 *bp,
                const PGeom &g, float theta, int nranges, uint8_t *ot, float *ov)
 {
-    hipLaunchKernelGGL((k_fire_pt<SK, NP, kMode, QC, TPC>), grid, dim3(kThreads), lds, s, xp, xw, bp, g,
+    hipLaunchKernelGGL((k_fire_pt<SK, NP, kMode, QC, TPC, kWin>), grid, dim3(kThreads), lds, s, xp, xw, bp, g,
                        theta, nranges, ot, ov);
 }
 
@@ -890,6 +967,8 @@ const PtExact kExact[] = {
     {18, 3, 2, 1, 32, &launch_pt<18, 2, 1, 3, 32>},
     {36, 12, 1, 3, 32, &launch_pt<36, 1, 3, 12, 32>},
 };
+// and with two windows of 8 steps (for 9 to 16)
+const PtExact kWindowed = {18, 6, 2, 3, 8, &launch_pt<18, 2, 3, 6, 8, true>};
 
 #define SPK_PT(S, N) {&launch_pt<S, N, 0>, &launch_pt<S, N, 1>, &launch_pt<S, N, 2>, &launch_pt<S, N, 3>}
 const PtLaunch kLaunch2[9][4] = {SPK_PT(2, 2),  SPK_PT(4, 2),  SPK_PT(6, 2),  SPK_PT(8, 2), SPK_PT(10, 2),
@@ -927,11 +1006,11 @@ const LbExact kLbExact[] = {
     {10, 2, 2, 1, 16, LbLayout<10, 2>::hal, &launch_lb<10, 2, 1, 2, 16, 12>},
 };
 
-template <int SKT, int NP, int kMode, int QC, int TPC, int NW, int KC>
+template <int SKT, int NP, int kMode, int QC, int TPC, int NW, int KC, bool kWin = false>
 void launch_lbk(dim3 grid, size_t lds, hipStream_t s, const uint8_t *xp, size_t xw, const h8 *bp,
                 const PGeom &g, float theta, int nranges, uint8_t *ot, float *ov)
 {
-    auto kern = k_fire_lbk<SKT, NP, kMode, QC, TPC, NW, KC>;
+    auto kern = k_fire_lbk<SKT, NP, kMode, QC, TPC, NW, KC, kWin>;
     static const bool attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  160 * 1024) == hipSuccess;
@@ -944,7 +1023,28 @@ void launch_lbk(dim3 grid, size_t lds, hipStream_t s, const uint8_t *xp, size_t 
 // row of 19 slices per chunk.
 const LbExact kLbkExact[] = {
     {57, 19, 2, 2, 16, LbkLayout<19, 2>::hal, &launch_lbk<57, 2, 2, 19, 16, 16, 19>},
+    {57, 19, 2, 2, 8, LbkLayout<19, 2>::hal, &launch_lbk<57, 2, 2, 19, 8, 16, 19, true>},
 };
+
+// A threshold below this part of a window's taps is likely crossed in the
+// first half of the steps where inputs are dense (the layers above: 0.037 and
+// 0.006).  Where it is not, windows cost up to a tenth (30 -> 250 maps at 20 %
+// firing, 0.096: 55 against 50 us): the second half of most tiles is computed
+// after all, and slices without a spike are rarer over four positions than two.
+constexpr float kLowTheta = 0.045f;
+
+// Whether a layer's kernel has an instance that takes its steps in two halves.
+bool windowed(const PGeom &g, bool half_w)
+{
+    const auto is = [&](int SK, int QC, int NP, int mode) {
+        return SK == g.SK && QC == g.Q16 && NP == (half_w ? 1 : 2) && mode == read_mode(g.Cp);
+    };
+    if (g.SKp == g.SK && is(kWindowed.SK, kWindowed.QC, kWindowed.NP, kWindowed.mode)) return true;
+    if (g.by * g.bx > 1) return false;
+    for (const LbExact &e : kLbkExact)
+        if (e.TP == 8 && is(e.SK, e.QC, e.NP, e.mode)) return true;
+    return false;
+}
 
 // Largest staged row range over the groups of every range (exact, per geometry).
 int max_rows(const PGeom &g, int nranges)
@@ -1031,6 +1131,10 @@ spk_status conv_fire_pt(const uint8_t *in, int B, int T, int Ci, int Hi, int Wi,
 {
     PGeom g = make_pgeom(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, half_w);
     g.SKp = packed_sk(g.SK, half_w);
+    if (T > 8 && T <= 16 && theta < kLowTheta * ((float)Ci * Kh * Kw) && windowed(g, half_w)) {
+        g.TP = 8;
+        g.lgTP = 3;
+    }
     uint8_t *xp = reinterpret_cast<uint8_t *>(ws);
     h8 *bp = reinterpret_cast<h8 *>(reinterpret_cast<char *>(ws) + xp_bytes(g));
     // a pooled input row stages its window rows past the row buffer when
@@ -1096,11 +1200,16 @@ spk_status conv_fire_pt(const uint8_t *in, int B, int T, int Ci, int Hi, int Wi,
             return check_launch("spk_conv_fire");
         }
     }
+    if (!instance_sk(g.SK, half_w)) {  // k_fire_deep takes all steps at once
+        g.TP = T <= 8 ? 8 : (T <= 16 ? 16 : 32);
+        g.lgTP = T <= 8 ? 3 : (T <= 16 ? 4 : 5);
+    }
     PtLaunch launch;
     if (instance_sk(g.SK, half_w)) {
         int idx = 0;
         while ((half_w ? kSK1 : kSK2)[idx] != g.SKp) idx++;
         launch = (half_w ? kLaunch1 : kLaunch2)[idx][read_mode(g.Cp)];
+        if (T > 8 && g.TP == 8) launch = kWindowed.fn;
         for (const PtExact &e : kExact)
             if (e.SK == g.SK && g.SKp == g.SK && e.QC == g.Q16 && e.NP == (half_w ? 1 : 2) &&
                 e.mode == read_mode(g.Cp) && e.TP == g.TP)

@@ -122,3 +122,27 @@ def test_list_driven_fire(case):
     o_tf, o_vk = oracle.conv_fire(t, w, T, s, p, theta)[:2]
     np.testing.assert_array_equal(np_(g_tf), o_tf)
     np.testing.assert_array_equal(np_(g_vk), o_vk)
+
+
+@pytest.mark.parametrize("Ci,Co,T,theta,dens", [
+    (30, 40, 15, 1.0, 0.9),     # every map crosses in the first window of 8 steps
+    (30, 70, 9, 11.0, 0.4),     # some cross in the second, some never; a window of one step
+    (25, 33, 16, 12.0, 0.15),
+    (100, 40, 15, 5.0, 0.8),    # the chunked kernel: one decision per group of 64 positions
+    (100, 33, 10, 40.0, 0.3),
+])
+def test_fire_in_windows_of_steps(Ci, Co, T, theta, dens):
+    """Low thresholds with 9 to 16 steps: tiles of 8 steps, the later ones only
+    where a map has not crossed.  Weights whose sums are exact in any order, one
+    part of them negative: potentials also fall."""
+    dev = gpu()
+    rng = np.random.default_rng(Ci + Co + T)
+    t = random_times(rng, (3, Ci, 9, 14), T, dens)
+    t[1] = np.where(t[1] < 8, NEVER, t[1])     # a sample whose spikes all come late
+    w = (np.round(rng.uniform(0.25, 0.999, size=(Co, Ci, 3, 3)) * 4096) / 4096).astype(np.float32)
+    w[: Co // 4] -= np.float32(0.625)
+    theta += 2.0 ** -14
+    g_tf, g_vk = spk.spk_conv_fire(_t(t, dev), _t(w, dev), T, 1, 1, theta)
+    o_tf, o_vk = oracle.conv_fire(t, w, T, 1, 1, theta)[:2]
+    np.testing.assert_array_equal(np_(g_tf), o_tf)
+    np.testing.assert_array_equal(np_(g_vk), o_vk)
