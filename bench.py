@@ -510,9 +510,10 @@ def main():
                            f"{pipe_call(wl, dom)} ({dom_name})"),
                 "kernel_ms": dom_ms,
                 "work": f"{work[dom][1]} = {work[dom][0]:.4g} flop per launch"}
-    if sparse_dom:
-        # the event conv does not compute the dense product: its frac is the
-        # dense-equivalent rate, above 1 where the skipped work outweighs
+    if sparse_dom or achieved > PEAK_F16_MFMA_TFLOPS:
+        # the event conv and the list-driven kernel compute only the taps that
+        # fire: the frac is the dense-equivalent rate, above 1 where the skipped
+        # work outweighs
         roofline["effective"] = True
         if per_layer:
             roofline["events_per_s"] = per_layer[0]["events_per_s"]

@@ -129,15 +129,18 @@ size_t spk::conv_least_workspace(int B, int T, int Ci, int Hi, int Wi, int Co, i
 static bool list_driven(int B, int T, int Ci, int Hi, int Wi, int Co, int Kh, int Kw, int stride, int pad,
                         int Ho, int Wo, bool half_w, bool readout, bool potentials, float theta)
 {
+    if (readout || potentials) return false;
+    const float part = theta / ((float)Ci * Kh * Kw);
+    const long long tiles = (long long)B * Ho * Wo * ((Co + 31) / 32);  // positions x 32 maps
+    const bool low = half_w && (T > 16 ? part < 0.2f && tiles >= 16384
+                                       : T > 8 && Ci >= 16 && part < 0.12f && tiles >= 65536);
+    // (the plan of the lists costs host time on each call: only where it can matter)
+    const bool staged = spk::conv_pt_supported(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, half_w, readout, potentials);
+    if (staged && !low) return false;
     bool wide = false;
     if (!spk::conv_ls_supported(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, half_w, readout, potentials, &wide))
         return false;
-    const float part = theta / ((float)Ci * Kh * Kw);
-    const long long tiles = (long long)B * Ho * Wo * ((Co + 31) / 32);  // positions x 32 maps
-    if (half_w && (T > 16 ? part < (wide ? 0.2f : 0.12f) && tiles >= 16384
-                          : T > 8 && Ci >= 16 && part < 0.12f && tiles >= 65536))
-        return true;
-    return !spk::conv_pt_supported(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, half_w, readout, potentials);
+    return !staged || T <= 16 || wide || part < 0.12f;
 }
 
 // Scratch of a call: what it cannot do without, or what the list-driven path takes.
