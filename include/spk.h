@@ -576,9 +576,12 @@ spk_status spk_spikes_to_times(const uint32_t *spikes, const int32_t *offsets, i
  *   spikes, offsets, cap  the input spike list over Ci x Hi x Wi neurons.
  *   w      Co x Ci x Kh x Kw (device): float master or IEEE half bits; float
  *          weights are added in float, in step order and tap order
- *          ((ky, kx, c) row-major) within a step.
+ *          ((ky, kx, c) row-major) within a step; half weights are added in
+ *          float as well, in an order that depends on the workspace given.
  *   ws     workspace of spk_conv_fire_sparse_workspace_size(...) bytes (a
- *          padded channels-last time buffer and the weight table).
+ *          time map with the spikes of each row and the weight table; the
+ *          padded channels-last time buffer and weight table that the float
+ *          path needs are enough for half weights too, at a lower speed).
  * Errors: SPK_E_ARG, SPK_E_SHAPE (T range, empty output, tensors of 2^31
  * elements, B > 65535), SPK_E_UNSUPPORTED (unknown dtype, or a weight table
  * of Kh*Kw*Ci taps x 32 maps that does not fit a block's LDS),

@@ -13,7 +13,8 @@
 // window into a short list and adds their weights to the potentials of every
 // map in step order, testing theta after each step that brought a spike.  A
 // lane owns one or two maps; their weights sit in LDS as a tap-major table,
-// so an arrival costs one LDS read and one add per map.
+// so an arrival costs one LDS read and one add per map.  Half weights of all
+// but small layers take the matrix-core kernel of spk_conv_ls.hip instead.
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
@@ -708,6 +709,27 @@ void launch_ev(dim3 grid, dim3 block, size_t lds, hipStream_t s, const uint8_t *
     hipLaunchKernelGGL((k_fire_ev<WT, MPL>), grid, block, lds, s, xp, wt, g, theta, nranges, ot, ov);
 }
 
+// Whether a layer's list is turned into a time map for the kernel of
+// spk_conv_ls.hip: half weights (their products are exact, only the order of the
+// float sums differs; float masters are added in float, in the documented order).
+// Calls in us, events / matrix: 64 -> 128 maps 3x3, 128 x 64 x 64, 30 steps at 5 %
+// 914 / 510, at 2 % 669 / 474; 40 -> 16 maps 5x5, 16 x 96 x 96 275 / 77; 6 -> 4
+// maps 195 / 43; at 90 % firing (16 -> 100 maps) 552 / 190.  Small layers gain
+// nothing (1 x 28 x 28, 64 -> 64 maps, 1568 tiles: 27 / 27) or lose to the pass
+// that lists rows (1 x 12 x 12, 144 tiles: 19 / 27); 3600 tiles: 65 / 43.
+bool ev_matrix(int B, int T, int Ci, int Hi, int Wi, int Co, int Kh, int Kw, int stride, int pad, bool half_w,
+               bool readout, size_t &map_bytes, size_t &bytes)
+{
+    const int Ho = spk_out_extent(Hi, Kh, stride, pad), Wo = spk_out_extent(Wi, Kw, stride, pad);
+    const long long tiles = (long long)B * Ho * Wo * ((Co + 31) / 32);  // positions x 32 maps
+    if (!half_w || B > 65535 || tiles < 2048 ||
+        !spk::conv_ls_supported(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, true, readout, false, nullptr))
+        return false;
+    map_bytes = spk::align_up((size_t)B * Ci * Hi * Wi, 256);
+    bytes = map_bytes + spk::conv_ls_workspace(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, Ho, Wo, true);
+    return true;
+}
+
 }  // namespace
 
 // ------------------------------------------------------------------ ABI
@@ -794,7 +816,10 @@ extern "C" size_t spk_conv_fire_sparse_workspace_size(int B, int T, int Ci, int 
     size_t lds;
     if (!ev_plan(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, w_dtype == SPK_F16, g, waves, lds))
         return 0;
-    return ev_xp_bytes(g) + spk::align_up((size_t)g.NCH * g.wchunk, 256);
+    size_t need = ev_xp_bytes(g) + spk::align_up((size_t)g.NCH * g.wchunk, 256), map = 0, full = 0;
+    if (ev_matrix(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, w_dtype == SPK_F16, false, map, full))
+        need = std::max(need, full);
+    return need;
 }
 
 extern "C" spk_status spk_conv_fire_sparse(const uint32_t *spikes, const int32_t *offsets, int cap,
@@ -835,10 +860,22 @@ extern "C" spk_status spk_conv_fire_sparse(const uint32_t *spikes, const int32_t
     SPK_REQUIRE(ws_bytes >= need, SPK_E_WORKSPACE, "spk_conv_fire_sparse: workspace %zu < %zu bytes",
                 ws_bytes, need);
     SPK_REQUIRE_WS_ALIGNED(ws, "spk_conv_fire_sparse");
+    hipStream_t s = spk::stream_of(stream);
+    size_t map = 0, full = 0;
+    if (ev_matrix(B, T, Ci, Hi, Wi, Co, Kh, Kw, stride, pad, half_w, theta > 3.4e38f, map, full) && ws_bytes >= full) {
+        uint8_t *x = static_cast<uint8_t *>(ws);
+        hipLaunchKernelGGL(k_fill_u8, dim3((unsigned)std::min<size_t>(4096, (map / 16 + 255) / 256 + 1)),
+                           dim3(256), 0, s, x, map, (uint8_t)spk::kNever);
+        if (cap > 0)
+            hipLaunchKernelGGL(k_list_place, dim3(std::min(64, (cap + 4095) / 4096), B), dim3(256), 0, s,
+                               spikes, offsets, cap, B, T, Ci, Hi, Wi, -1, x);
+        SPK_LAUNCHED("spk_conv_fire_sparse");
+        return spk::conv_fire_ls(x, B, T, Ci, Hi, Wi, w, true, Co, Kh, Kw, stride, pad, Ho, Wo, theta,
+                                 out_times, out_vkey, x + map, s, nullptr);
+    }
     g.vec = (g.HoWo % 4 == 0) && ((uintptr_t)out_times % 4 == 0) && ((uintptr_t)out_vkey % 16 == 0);
     uint8_t *xp = static_cast<uint8_t *>(ws);
     uint8_t *wt = xp + ev_xp_bytes(g);
-    hipStream_t s = spk::stream_of(stream);
     // padded channels-last time buffer: all "never" (T), then the stored spikes
     const size_t xb = ev_xp_bytes(g);
     hipLaunchKernelGGL(k_fill_u8, dim3((unsigned)std::min<size_t>(4096, (xb / 16 + 255) / 256 + 1)),

@@ -146,3 +146,38 @@ def test_fire_in_windows_of_steps(Ci, Co, T, theta, dens):
     o_tf, o_vk = oracle.conv_fire(t, w, T, 1, 1, theta)[:2]
     np.testing.assert_array_equal(np_(g_tf), o_tf)
     np.testing.assert_array_equal(np_(g_vk), o_vk)
+
+
+@pytest.mark.parametrize("B,Ci,H,W,Co,K,T,part,dens,cap,small", [
+    (1, 9, 32, 63, 32, 3, 20, 0.05, 0.1, 0, False),      # 2016 tiles: the event kernel
+    (1, 9, 32, 64, 32, 3, 20, 0.05, 0.1, 0, False),      # 2048 tiles: the matrix cores
+    (1, 9, 32, 64, 32, 3, 20, 0.05, 0.1, 0, True),       # and without the scratch for them
+    (3, 7, 31, 27, 33, 5, 45, 0.05, 0.9, 0, False),      # odd sizes, two windows of steps, dense
+    (2, 12, 40, 30, 5, 3, 254, 0.1, 0.3, 500, False),    # spikes past the list's capacity
+])
+def test_list_half_weights(B, Ci, H, W, Co, K, T, part, dens, cap, small, monkeypatch):
+    """Weights are multiples of 2^-11 with exact sums: every output equals the oracle's."""
+    dev = gpu()
+    rng = np.random.default_rng(B * 100 + W + T)
+    t = random_times(rng, (B, Ci, H, W), T, dens)
+    w = (np.round(rng.uniform(0.25, 0.999, size=(Co, Ci, K, K)) * 2048) / 2048).astype(np.float32)
+    w[: Co // 4] -= np.float32(0.625)
+    theta = round(part * Ci * K * K) + 2.0 ** -14
+    sp, off = spk.spk_times_to_spikes(_t(t, dev), T, cap or Ci * H * W)
+    x = np_(spk.spk_spikes_to_times(sp, off, (Ci, H, W), T))
+    if small:
+        lib = spk.load()
+        full = lib.spk_conv_fire_sparse_workspace_size
+
+        class Less:
+            def __getattr__(self, name):
+                return getattr(lib, name)
+
+            def spk_conv_fire_sparse_workspace_size(self, *a):
+                return full(*a) - 1
+
+        monkeypatch.setattr(spk, "load", Less)
+    g_tf, g_vk = spk.spk_conv_fire_sparse(sp, off, (Ci, H, W), _t(w, dev).half(), T, 1, K // 2, theta)
+    o_tf, o_vk = oracle.conv_fire(x, w, T, 1, K // 2, theta)[:2]
+    np.testing.assert_array_equal(np_(g_tf), o_tf)
+    np.testing.assert_array_equal(np_(g_vk), o_vk)
